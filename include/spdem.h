@@ -201,7 +201,7 @@ sp_status sp_step(sp_ctx* ctx, double dt, int64_t nsteps);
  * k > 1 (sp_set_step_block) the fine steps up to each update run as blocked
  * launches of at most k steps,
  * the update done inside the launch that ends at it.  Cadence state lives in
- * the context: a ring of N0 x ncells x 128 B statistics.
+ * the context: a ring of N0 x ncells x 40 B statistics.
  * Errors: SP_EINVAL (a value < 1, N0 or N1 > SP_MAX_COUPLING), SP_ESTATE
  * (N0 > 1 with SP_NO_CONTINUUM or an active hybrid), SP_ENOMEM at the first
  * coupled sp_step.  sp_hybrid_set, sp_step_hybrid, sp_closure_sample and
@@ -313,18 +313,17 @@ sp_status sp_set_batching(sp_ctx* ctx, const int32_t* waves, const int32_t* pers
 /* Tune the batching of the launches sp_step runs, on a scratch copy of the
  * floe state (the simulation is not advanced; candidate lists are rebuilt at
  * the next step).  With blocked steps (block length > 1 at the plain cadence,
- * see sp_set_step_block): every non-empty bucket alone over the wavefronts per
- * cell of its blocked launches that hold one floe per lane (W = 1, 2, 4, 8,
- * 16), then the block length (16, 32 or 64 steps) over the whole step; each
- * variant one warm-up launch and the minimum of reps timed launches; *best_ms
- * receives the best whole step's time per step.  Otherwise (per-step launches)
+ * see sp_set_step_block): the block length (16, 32 or 64 steps) over the whole
+ * step, each one warm-up launch and the minimum of reps timed launches;
+ * *best_ms receives the best whole step's time per step.  Otherwise (per-step launches)
  * every (waves, persistent) variant of every bucket's per-step kernel, reps
  * repetitions of two steps each; *best_ms the summed best step time of the
  * buckets.  *best_ms may be NULL.  Synchronises.
  * Errors: SP_EINVAL, SP_ESTATE, SP_ENOMEM, SP_EDEVICE. */
 sp_status sp_autotune(sp_ctx* ctx, double dt, int32_t reps, double* best_ms);
-/* Wavefronts per cell of each bucket's blocked launches (0 for an empty
- * bucket), as sp_autotune or the defaults set them. */
+/* Nominal wavefronts per cell of each bucket's blocked launches (0 for an empty
+ * bucket): what its largest cell count can need, rounded to the next of 1, 2,
+ * 4, 8, 16.  A launch takes ceil(n / 64) for its own cells (<= this). */
 sp_status sp_get_block_waves(sp_ctx* ctx, int32_t* waves);
 
 /* Temporal blocking of the plain step (coarse step = fine step): with k > 1,
@@ -333,22 +332,23 @@ sp_status sp_get_block_waves(sp_ctx* ctx, int32_t* waves);
  * (the cell DEMs never read the continuum at this cadence), each step's
  * statistics going to a k-slot ring, followed by the k continuum updates;
  * a call's remaining steps (fewer than k) run as one block of their own
- * length, so every step of sp_step is blocked and none captures a graph.  Blocked launches hold one floe per lane: a
- * bucket whose cells exceed 64 W floes runs them with W = 8 (up to 512 floes)
- * or 16 (up to SP_MAX_CELL_FLOES).  Applies to sp_step with N0 = 1 (the coupled cadence
+ * length, so every step of sp_step is blocked and none captures a graph.  Blocked launches hold one floe per lane,
+ * a cell of n floes in ceil(n / 64) wavefronts (a bucket's launches group its
+ * cells by that number).  Applies to sp_step with N0 = 1 (the coupled cadence
  * blocks its stretches between
  * coarse-to-fine updates, the hybrid its DEM cells between checks: see
  * sp_set_coupling and sp_step_hybrid).  The floe state is the same
  * bit for bit as with k = 1; statistics are summed in another fixed order.
  * With SP_TANGENTIAL_SPRING the contact history is staged in LDS as well.
- * Ring: k x ncells x 128 B.  Default 32.  Errors: SP_EINVAL (k outside
+ * Ring: 2 x k x ncells x 40 B.  Default 32.  Errors: SP_EINVAL (k outside
  * [1, SP_MAX_STEP_BLOCK]). */
 #define SP_MAX_STEP_BLOCK 1024
 sp_status sp_set_step_block(sp_ctx* ctx, int32_t k);
 /* The block length and whether blocked steps currently apply (1) or not (0). */
 sp_status sp_get_step_block(sp_ctx* ctx, int32_t* k, int32_t* active);
 /* Work counted by blocked steps since sp_set_floes: candidate-list entries
- * tested (over floes and steps) and the steps taken in blocks (either may be
+ * decided (over floes and steps; the near ones tested exactly, the others by
+ * the displacement bound) and the steps taken in blocks (either may be
  * NULL).  Synchronises. */
 sp_status sp_get_work(sp_ctx* ctx, int64_t* candidate_tests, int64_t* blocked_steps);
 

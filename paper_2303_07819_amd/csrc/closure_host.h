@@ -203,11 +203,10 @@ __device__ __forceinline__ void base_cell(int C, const double* Q, const ClosureA
 
 // Base-updated state of every cell: Qb [4][nc].
 // The reduced DEM statistics of every cell at a.t (a.rs must be null).
-// Every cell's reduced statistics into rs; with row and mom, a closure cell
-// (row[C] >= 0) also writes its coefficient <v> into its statistics row of mom,
-// which its DEM neighbours' continuum stencils read.
-__global__ void reduced_stats_kernel(ClosureArgs a, double* rs, const int32_t* row = nullptr,
-                                     double* mom = nullptr)
+// Every cell's reduced statistics into rs; with row, a closure cell (row[C] >=
+// 0) also writes its coefficient <v> into the step's statistics (ub, vb at C *
+// stride), which its DEM neighbours' continuum stencils read.
+__global__ void reduced_stats_kernel(ClosureArgs a, double* rs, const int32_t* row, double* ub, double* vb, int stride)
 {
     const int C = blockIdx.x * blockDim.x + threadIdx.x;
     if (C >= a.nx * a.ny) return;
@@ -215,9 +214,9 @@ __global__ void reduced_stats_kernel(ClosureArgs a, double* rs, const int32_t* r
     reduced_stats(C, a.red, a.mf, a.oc, a.t, o);
 #pragma unroll
     for (int k = 0; k < 5; ++k) rs[(size_t)C * 5 + k] = o[k];
-    if (mom && row[C] >= 0) {
-        mom[(size_t)C * kMomStride + M_UBAR] = o[0];
-        mom[(size_t)C * kMomStride + M_VBAR] = o[1];
+    if (row && row[C] >= 0) {
+        ub[(size_t)C * stride] = o[0];
+        vb[(size_t)C * stride] = o[1];
     }
 }
 

@@ -22,8 +22,8 @@
 
 namespace spdem {
 
-// mean[i] = (sum over the window's slots, oldest first) / N0, i over
-// ncells x kMomStride statistics.
+// mean[i] = (sum over the window's slots, oldest first) / N0, i over the
+// kRing x ncells statistics of a slot.
 __global__ __launch_bounds__(256) void window_mean_kernel(const double* ring, int N0, size_t slot_len, double* mean)
 {
     const size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
@@ -108,10 +108,10 @@ sp_status coupling_prepare(sp_ctx* c)
 {
     if (c->cpl_ring && c->cpl_ring_slots == c->N0) return SP_OK;
     coupling_free(c);
-    const size_t slot = (size_t)c->ncells * kMomStride;
+    const size_t slot = (size_t)c->ncells * kRing;
     SP_TRY(dalloc(c, &c->cpl_ring, slot * (size_t)c->N0));
     SP_TRY(dalloc(c, &c->cpl_mean, slot));
-    SP_TRY(dalloc(c, &c->cpl_x0, slot));
+    SP_TRY(dalloc(c, &c->cpl_x0, (size_t)c->ncells * kMomStride));
     SP_TRY(dalloc(c, &c->cpl_count, 2));
     SP_TRY(dalloc(c, &c->cpl_rreq, 1));
     HIP_TRY(c, hipMemsetAsync(c->cpl_ring, 0, slot * (size_t)c->N0 * 8, c->stream));
@@ -133,14 +133,15 @@ sp_status coupling_prepare(sp_ctx* c)
 // the result in both continuum buffers, then X0 of the next coarse step.
 sp_status coarse_step(sp_ctx* c, double dt)
 {
-    const size_t slot = (size_t)c->ncells * kMomStride;
+    const size_t slot = (size_t)c->ncells * kRing;
     hipLaunchKernelGGL(window_mean_kernel, dim3((unsigned)((slot + 255) / 256)), dim3(256), 0, c->stream,
                        c->cpl_ring, c->N0, slot, c->cpl_mean);
     HIP_TRY(c, hipGetLastError());
     const double dTs = (double)c->N0 * dt / (double)c->N1;
     const double inv_area = 1.0 / (c->p.cell_lx * c->p.cell_ly);
     for (int i = 0; i < c->N1; ++i) {
-        hipLaunchKernelGGL(lf_kernel, dim3((c->ncells + 63) / 64), dim3(64), 0, c->stream, c->cpl_mean, c->Q[i & 1],
+        hipLaunchKernelGGL(lf_kernel, dim3((c->ncells + 63) / 64), dim3(64), 0, c->stream,
+                           stats_of_slot(c->cpl_mean, c->ncells), c->Q[i & 1],
                            c->Q[(i + 1) & 1], c->p.nx, c->p.ny, dTs, c->p.cell_lx, c->p.cell_ly, inv_area,
                            c->cfl_bits_d, c->err_d, wall_x(c));
         HIP_TRY(c, hipGetLastError());
@@ -189,7 +190,7 @@ sp_status nudge(sp_ctx* c, double frac)
 sp_status coupled_steps(sp_ctx* c, const StepArgs& args, int64_t nsteps)
 {
     SP_TRY(coupling_prepare(c));
-    const size_t slot = (size_t)c->ncells * kMomStride;
+    const size_t slot = (size_t)c->ncells * kRing;
     // the step arguments, made again after every coarse step: its re-plan of
     // the contact search changes the sub-bins, the skin and the list buffers
     StepArgs base = args;

@@ -47,6 +47,7 @@ static_assert(kListCap % 8 == 0 && kListCap <= 32, "candidate lists: groups of e
 constexpr int kMaxBinsSide = 32;
 constexpr double kPi = 3.14159265358979323846;
 constexpr float kGuard = 1.0f / 524288.0f;  // 2^-19
+constexpr float kTestPad = 1.0f + 1.0f / 262144.0f;   // 1 + 2^-18: radii padded for the blocked kernel's candidate test
 constexpr int kDyn = 8;                 // statistics reduced by every step
 constexpr int kSpringBytes = SP_SPRING_CAP * 8 + 16;   // LDS per floe of a blocked spring launch's contact history
 
@@ -56,6 +57,12 @@ constexpr uint32_t kErrNaN = 2u;
 constexpr uint32_t kErrCFL = 4u;
 constexpr uint32_t kErrCapacity = 8u;
 constexpr uint32_t kErrWall = 16u;
+
+// Statistics of one step that the continuum reads, as one array of ncells
+// values each (neighbouring cells side by side): the coefficients <v> = U / n
+// and the sums of ocean drag and drag torque.
+enum { R_UBAR = 0, R_VBAR, R_SVX, R_SVY, R_SW };
+constexpr int kRing = 5;
 
 enum { M_N = 0, M_MASS, M_PX, M_PY, M_L, M_UX, M_UY, M_SVX, M_SVY, M_SW, M_AICE, M_UBAR, M_VBAR };
 
@@ -67,6 +74,8 @@ struct Modes {
     double cz[SP_MAX_MODES];  // curl coefficient av kx - au ky
     int direct;               // every phase offset |kxL fx + kyL fy| (|fx|, |fy| <= 1/2) is <= 1.6
 };
+
+struct ModeC;
 
 struct StepArgs {
     // floe state, SoA sorted by cell
@@ -80,8 +89,10 @@ struct StepArgs {
     const float* h;
     const int32_t* cell_start;
     const double2* phase;      // [ncells][nmodes]: (sin, cos) of the phase at the cell centre
+    const ModeC* modec;        // [ncells][nmodes]: mode_consts of the same
     double* mom;               // statistics written by this step [ncells][kMomStride]
     double* mom_alt;           // where the statistics of work entries with w = 1 go instead
+    double* ring_slot;         // not null: the step's statistics go here instead, as R_UBAR .. R_SW [kRing][ncells]
     uint32_t* err;
     unsigned long long* contacts;   // [ncells] contacts counted per cell since the floes were set
     unsigned long long* cands;
@@ -145,24 +156,37 @@ __device__ __forceinline__ float wave_max_f32(float x)
 // zeros shifted in), then rows 1 and 3 take the last lane of rows 0 and 2
 // (row_bcast:15) and rows 2 and 3 that of row 1 (row_bcast:31); lane 63 holds
 // the maximum and every lane returns it.  No LDS traffic.
+// Nonnegative floats order as their bit patterns, so the maxima are integer
+// ones (a single instruction with its DPP operand; the float maximum first
+// quiets each operand).
 template <int CTRL, int ROWS>
-__device__ __forceinline__ float dpp_f32(float x)
+__device__ __forceinline__ uint32_t dpp_max_u32(uint32_t x)
 {
-    // a row shift with every row enabled writes every lane (zero where the
-    // source lies outside the row): no old value to keep
-    if (CTRL < 0x140 && ROWS == 0xf) return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(x), CTRL, 0xf, 0xf, true));
-    return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), CTRL, ROWS, 0xf, CTRL < 0x140));
+    const uint32_t y = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, CTRL, ROWS, 0xf, CTRL < 0x140);
+    return x > y ? x : y;
 }
 
-__device__ __forceinline__ float wave_max_nonneg(float x)
+// The same over the first 16 lanes of the wavefront (every lane returns it).
+__device__ __forceinline__ float row_max_nonneg(float f)
 {
-    x = fmaxf(x, dpp_f32<0x111, 0xf>(x));
-    x = fmaxf(x, dpp_f32<0x112, 0xf>(x));
-    x = fmaxf(x, dpp_f32<0x114, 0xf>(x));
-    x = fmaxf(x, dpp_f32<0x118, 0xf>(x));
-    x = fmaxf(x, dpp_f32<0x142, 0xa>(x));
-    x = fmaxf(x, dpp_f32<0x143, 0xc>(x));
-    return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(x), 63));
+    uint32_t x = __float_as_uint(f);
+    x = dpp_max_u32<0x111, 0xf>(x);
+    x = dpp_max_u32<0x112, 0xf>(x);
+    x = dpp_max_u32<0x114, 0xf>(x);
+    x = dpp_max_u32<0x118, 0xf>(x);
+    return __int_as_float(__builtin_amdgcn_readlane((int)x, 15));
+}
+
+__device__ __forceinline__ float wave_max_nonneg(float f)
+{
+    uint32_t x = __float_as_uint(f);
+    x = dpp_max_u32<0x111, 0xf>(x);
+    x = dpp_max_u32<0x112, 0xf>(x);
+    x = dpp_max_u32<0x114, 0xf>(x);
+    x = dpp_max_u32<0x118, 0xf>(x);
+    x = dpp_max_u32<0x142, 0xa>(x);
+    x = dpp_max_u32<0x143, 0xc>(x);
+    return __int_as_float(__builtin_amdgcn_readlane((int)x, 63));
 }
 
 // Square root of a finite x >= 0 (the drag speed): the hardware reciprocal
@@ -201,15 +225,20 @@ __device__ __forceinline__ void root_and_reciprocal(double x, double& d, double&
 }
 
 // FP64 contact predicate: (dx*dx + dy*dy) < R*R without contraction.
-__device__ __noinline__ bool exact_contact(int dxi, int dyi, float rl, float rj, double qxd,
-                                           double qyd)
+__device__ __forceinline__ bool exact_contact_inline(int dxi, int dyi, double rl, double rj, double qxd, double qyd)
 {
 #pragma clang fp contract(off)
     double dx = (double)dxi * qxd;
     double dy = (double)dyi * qyd;
-    double R = (double)rl + (double)rj;
+    double R = rl + rj;
     double d2 = dx * dx + dy * dy;
     return d2 < R * R;
+}
+
+__device__ __noinline__ bool exact_contact(int dxi, int dyi, float rl, float rj, double qxd,
+                                           double qyd)
+{
+    return exact_contact_inline(dxi, dyi, (double)rl, (double)rj, qxd, qyd);
 }
 
 // FP32 screen value d^2 - R^2 and R^2.
@@ -278,10 +307,18 @@ __device__ __forceinline__ void sincos_direct(float x, float& s, float& c)
 // (au, av), cz its curl coefficient and theta_c its phase at the cell centre
 // (S = sin theta_c, C = cos theta_c): the products au S, au C, av S, av C,
 // cz C, -cz S in FP64, and the mode's phase per cell fraction kx Lx, ky Ly.
-struct ModeC {
+struct __align__(64) ModeC {
     double aS, aC, bS, bC, zC, zS;
     float kxL, kyL;
+    double unused;   // 64 bytes: one scalar load
 };
+
+// A cell's constants in memory that no kernel running beside writes: read at a
+// wavefront-uniform address they come through the scalar cache, and the
+// multiply-adds take them from scalar registers.
+typedef double ModeWords __attribute__((ext_vector_type(8)));
+typedef const ModeWords __attribute__((address_space(4)))* ModeTable;
+static_assert(sizeof(ModeC) == sizeof(ModeWords), "a mode's constants are one vector of the table");
 
 __device__ __forceinline__ void mode_consts(const Modes& md, int m, double2 sc, ModeC* mc)
 {
@@ -295,7 +332,17 @@ __device__ __forceinline__ void mode_consts(const Modes& md, int m, double2 sc, 
     q.zS = -(cz * sc.x);
     q.kxL = md.kxL[m];
     q.kyL = md.kyL[m];
+    q.unused = 0.0;
     mc[m] = q;
+}
+
+// The constants of every cell and mode, [ncells][nmodes].
+__global__ void mode_table_kernel(int ncells, int nmodes, Modes md, const double2* phase, ModeC* out)
+{
+    const size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (i >= (size_t)ncells * nmodes) return;
+    const int m = (int)(i % nmodes);
+    mode_consts(md, m, phase[i], out + (i - m));
 }
 
 // Ocean current (sum of a sin theta) and curl (sum of cz cos theta) at cell
@@ -310,32 +357,79 @@ __device__ __forceinline__ void mode_consts(const Modes& md, int m, double2 sc, 
 // to 3e-7 of their scale, ten times what the FP32 storage of the state does.
 // DIRECT: every |d| <= 1.6.
 template <bool DIRECT>
+__device__ __forceinline__ void ocean_mode(float fx, float fy, float kxL, float kyL, double aS, double aC, double bS,
+                                           double bC, double zC, double zS, double& uo, double& vo, double& zeta)
+{
+    const float d = kxL * fx + kyL * fy;
+    float sdf, cdf;
+    if (DIRECT)
+        sincos_direct(d, sdf, cdf);
+    else
+        sincos_small(d, sdf, cdf);
+    const double sd = sdf, cd = cdf;
+    uo = fma(aC, sd, fma(aS, cd, uo));
+    vo = fma(bC, sd, fma(bS, cd, vo));
+    zeta = fma(zS, sd, fma(zC, cd, zeta));
+}
+
+template <bool DIRECT>
 __device__ __forceinline__ void ocean_modes_t(float fx, float fy, const ModeC* mc, int nmodes, double& uo,
                                               double& vo, double& zeta)
 {
 #pragma unroll 2
     for (int m = 0; m < nmodes; ++m) {
         const ModeC q = mc[m];
-        const float d = q.kxL * fx + q.kyL * fy;
-        float sdf, cdf;
-        if (DIRECT)
-            sincos_direct(d, sdf, cdf);
-        else
-            sincos_small(d, sdf, cdf);
-        const double sd = sdf, cd = cdf;
-        uo = fma(q.aC, sd, fma(q.aS, cd, uo));
-        vo = fma(q.bC, sd, fma(q.bS, cd, vo));
-        zeta = fma(q.zS, sd, fma(q.zC, cd, zeta));
+        ocean_mode<DIRECT>(fx, fy, q.kxL, q.kyL, q.aS, q.aC, q.bS, q.bC, q.zC, q.zS, uo, vo, zeta);
     }
 }
 
-__device__ __forceinline__ void ocean_modes(float fx, float fy, const ModeC* mc, int nmodes, bool direct,
+// The same from a cell's table in memory (16 scalar registers a mode, two
+// modes loaded together).
+template <bool DIRECT>
+__device__ __forceinline__ void ocean_mode_words(float fx, float fy, ModeWords q, double& uo, double& vo, double& zeta)
+{
+    ocean_mode<DIRECT>(fx, fy, __int_as_float(__double2loint(q[6])), __int_as_float(__double2hiint(q[6])), q[0], q[1],
+                       q[2], q[3], q[4], q[5], uo, vo, zeta);
+}
+
+template <bool DIRECT>
+__device__ __forceinline__ void ocean_modes_t(float fx, float fy, ModeTable mt, int nmodes, double& uo, double& vo,
+                                              double& zeta)
+{
+    int m = 0;
+#pragma unroll 1
+    for (; m + 1 < nmodes; m += 2) {
+        const ModeWords p = mt[m], q = mt[m + 1];
+        ocean_mode_words<DIRECT>(fx, fy, p, uo, vo, zeta);
+        ocean_mode_words<DIRECT>(fx, fy, q, uo, vo, zeta);
+    }
+    if (m < nmodes) ocean_mode_words<DIRECT>(fx, fy, mt[m], uo, vo, zeta);
+}
+
+template <class Table>
+__device__ __forceinline__ void ocean_modes(float fx, float fy, Table mc, int nmodes, bool direct,
                                             double& uo, double& vo, double& zeta)
 {
     if (direct)
         ocean_modes_t<true>(fx, fy, mc, nmodes, uo, vo, zeta);
     else
         ocean_modes_t<false>(fx, fy, mc, nmodes, uo, vo, zeta);
+}
+
+// Quadratic ocean drag and drag torque of a floe of radius r at the velocity
+// (du, dv) of the water relative to it and the curl zeta, FP64; cdpi = C_d rho_o
+// pi.  The fused products are written out: every kernel rounds alike.
+__device__ __forceinline__ void drag_terms(double du, double dv, double zeta, double w, double r, double cdpi,
+                                           double& fx, double& fy, double& t)
+{
+    const double sp = sqrt_nonneg(fma(dv, dv, du * du));
+    const double alpha = cdpi * r * r;
+    fx = alpha * du * sp;
+    fy = alpha * dv * sp;
+    const double dW = fma(zeta, 0.5, -w);
+    const double r2 = r * r;
+    const double beta = cdpi * r2 * r2 * r;
+    t = beta * dW * fabs(dW);
 }
 
 // Contact of floe l (radius rld, velocity (uld, vld), spin wld) with floe j at
@@ -353,9 +447,9 @@ __device__ __forceinline__ void ocean_modes(float fx, float fy, const ModeC* mc,
 // the pair's displacement xi_old (0 for a new contact) grows by v_t dt, the
 // force is c G xi, and past mu |F_n| the contact slips (the force at the
 // Coulomb limit, xi the displacement that gives it); xi receives the new value.
-template <bool SPRING = false>
+template <bool SPRING = false, class Args>
 __device__ __forceinline__ bool contact_terms(int dxi, int dyi, double rld, double uld, double vld, double wld,
-                                              float rj, float4 vj, bool lower, const StepArgs& a, double& cx,
+                                              float rj, float4 vj, bool lower, const Args& a, double& cx,
                                               double& cy, double& ct, double xi_old = 0.0, double* xi = nullptr)
 {
     const double dx = (double)dxi * a.qxd, dy = (double)dyi * a.qyd;
@@ -440,33 +534,12 @@ __device__ __forceinline__ double dpp_perm(double x)
     return __hiloint2double(hi, lo);
 }
 
-// Row totals (16 lanes) of eight values per lane by a transposing exchange:
-// at each stage a lane keeps half of its values and adds its partner's copy of
-// that half (partners: lane i ^ 8 by row_ror:8, i ^ 7 by row_half_mirror,
-// i ^ 2 and i ^ 1 by quad permutes), so lane i of a row ends with the row
-// total of value i >> 1 (both lanes of a pair hold it).  About half the
-// instructions of eight row sums.  Every lane of the wavefront must be active.
-__device__ __forceinline__ double row_sum8(const double (&v)[8], int lane)
-{
-    const bool b3 = lane & 8, b2 = lane & 4, b1 = lane & 2;
-    double a4[4];
-#pragma unroll
-    for (int j = 0; j < 4; ++j)
-        a4[j] = (b3 ? v[j + 4] : v[j]) + dpp_perm<0x128>(b3 ? v[j] : v[j + 4]);
-    double a2[2];
-#pragma unroll
-    for (int j = 0; j < 2; ++j)
-        a2[j] = (b2 ? a4[j + 2] : a4[j]) + dpp_perm<0x141>(b2 ? a4[j] : a4[j + 2]);
-    const double a1 = (b1 ? a2[1] : a2[0]) + dpp_perm<0x4e>(b1 ? a2[0] : a2[1]);
-    return a1 + dpp_perm<0xb1>(a1);
-}
-
 // Exclusive scan of cnt[0..nb) into start[0..nb] by the G threads of a group
-// (thread gt of group g); nb <= 16 G.  Every thread of the workgroup calls it.
-template <int G>
-__device__ void group_exclusive_scan(const int* cnt, int* start, int nb, int gt, int* wsum)
+// (thread gt of the group; wsum one entry per wavefront of it).  Every thread of
+// the workgroup calls it.
+__device__ __forceinline__ void group_exclusive_scan(const int* cnt, int* start, int nb, int gt, int G, int* wsum)
 {
-    constexpr int W = G / 64;
+    const int W = G >> 6;
     const int lane = gt & 63, wave = gt >> 6;
     const int ch = (nb + G - 1) / G;
     const int b0 = gt * ch;
@@ -481,7 +554,6 @@ __device__ void group_exclusive_scan(const int* cnt, int* start, int nb, int gt,
     if (lane == 63) wsum[wave] = incl;
     __syncthreads();
     int run = incl - tot;
-#pragma unroll
     for (int k = 0; k < W; ++k) run += (k < wave) ? wsum[k] : 0;
     for (int k = 0; k < ch; ++k) {
         if (b0 + k < nb) start[b0 + k] = run;
@@ -508,14 +580,14 @@ __device__ __forceinline__ void list_append(uint16_t* lst, int* cnt, int to, int
 // Screen the candidates q in [q0, q1) of the sorted copy against floe o; the
 // next candidate is loaded while the current one is screened.
 __device__ __forceinline__ void sweep(const uint4* S, int q0, int q1, uint32_t xl, uint32_t yl,
-                                     float rl, int o, uint16_t* lst, int* cnt, const StepArgs& a)
+                                     float rl, int o, uint16_t* lst, int* cnt, float qx, float qy)
 {
     if (q0 >= q1) return;
     uint4 pj = S[q0];
     for (int q = q0; q < q1; ++q) {
         const uint4 nxt = S[min(q + 1, q1 - 1)];
         float diff, R2;
-        screen((int)(pj.x - xl), (int)(pj.y - yl), rl, __uint_as_float(pj.z), a.qx, a.qy, diff, R2);
+        screen((int)(pj.x - xl), (int)(pj.y - yl), rl, __uint_as_float(pj.z), qx, qy, diff, R2);
         if (diff < kGuard * R2) {
             const int o2 = (int)(pj.w & 0xffffu);
             list_append(lst, cnt, o, o2);
@@ -606,15 +678,53 @@ __device__ __forceinline__ void lf_from_ops(int C, const double* o, double* Qn, 
     if (cfl > 1.0) atomicOr(err, kErrCFL);
 }
 
-__device__ __forceinline__ void lf_cell(int C, const double* mom, const double* Q, double* Qn,
+// The statistics a continuum step reads: the coefficients <v> and the sums of
+// drag and drag torque of cell C at index C * stride, from the statistics rows
+// of the per-step path (kMomStride values per cell) or from one slot of a
+// blocked launch's ring (one array per statistic).
+struct CellStats {
+    const double *ub, *vb, *sx, *sy, *sw;
+    int stride;
+};
+
+__host__ __device__ __forceinline__ CellStats stats_of_rows(const double* mom)
+{
+    return CellStats{mom + M_UBAR, mom + M_VBAR, mom + M_SVX, mom + M_SVY, mom + M_SW, kMomStride};
+}
+
+__host__ __device__ __forceinline__ CellStats stats_of_slot(const double* slot, int ncells)
+{
+    const size_t n = (size_t)ncells;
+    return CellStats{slot + R_UBAR * n, slot + R_VBAR * n, slot + R_SVX * n, slot + R_SVY * n, slot + R_SW * n, 1};
+}
+
+__device__ __forceinline__ void lf_cell(int C, const CellStats& st, const double* Q, double* Qn,
                                         int nx, int ny, double dT, double dX, double dY,
                                         double inv_area, unsigned long long* max_cfl_bits,
                                         uint32_t* err, bool wall)
 {
+    const LfNeighbours b = lf_neighbours(C, nx, ny, wall);
+    const int nc = nx * ny;
+    const size_t m = (size_t)st.stride;
     double o[kLfOps];
 #pragma unroll
-    for (int t = 0; t < kLfOps; ++t) o[t] = lf_operand(C, t, mom, Q, nx, ny, wall);
-    lf_from_ops(C, o, Qn, nx * ny, dT, dX, dY, inv_area, max_cfl_bits, err);
+    for (int f = 0; f < 4; ++f) {
+        const double* q = Q + (size_t)f * nc;
+        o[4 * f] = b.E < 0 ? 0.0 : q[b.E];
+        o[4 * f + 1] = b.W < 0 ? 0.0 : q[b.W];
+        o[4 * f + 2] = q[b.N];
+        o[4 * f + 3] = q[b.S];
+    }
+    o[16] = b.E < 0 ? 0.0 : st.ub[b.E * m];
+    o[17] = b.W < 0 ? 0.0 : st.ub[b.W * m];
+    o[18] = st.vb[b.N * m];
+    o[19] = st.vb[b.S * m];
+    o[20] = st.ub[C * m];
+    o[21] = st.vb[C * m];
+    o[22] = st.sw[C * m];
+    o[23] = st.sx[C * m];
+    o[24] = st.sy[C * m];
+    lf_from_ops(C, o, Qn, nc, dT, dX, dY, inv_area, max_cfl_bits, err);
 }
 
 // ------------------------------------------------------------- DEM step
@@ -710,7 +820,7 @@ __global__ __launch_bounds__(W >= 4 ? 64 * W : 256) void dem_step_kernel(StepArg
                 rank[i] = atomicAdd(&bcnt[b], 1);
             }
             __syncthreads();
-            group_exclusive_scan<G>(bcnt, bstart, nb, gt, wsum[g]);
+            group_exclusive_scan(bcnt, bstart, nb, gt, G, wsum[g]);
             for (int i = gt; i < nb_build; i += G) {
                 uint4 p = P[i];
                 p.w = (uint32_t)i | ((uint32_t)binof[i] << 16);
@@ -753,29 +863,29 @@ __global__ __launch_bounds__(W >= 4 ? 64 * W : 256) void dem_step_kernel(StepArg
                 const float rl = __uint_as_float(own.z) + a.skin;
                 if (a.nbx >= 3 && bx + 1 < a.nbx) {
                     // own-bin tail and the east bin are contiguous
-                    sweep(S, t + 1, bstart[b + 2], own.x, own.y, rl, o, lst, cnt, a);
+                    sweep(S, t + 1, bstart[b + 2], own.x, own.y, rl, o, lst, cnt, a.qx, a.qy);
                 } else {
-                    sweep(S, t + 1, bstart[b + 1], own.x, own.y, rl, o, lst, cnt, a);
+                    sweep(S, t + 1, bstart[b + 1], own.x, own.y, rl, o, lst, cnt, a.qx, a.qy);
                     if (a.nbx >= 3) {
                         const int be = by * a.nbx;   // east neighbour across the seam
-                        sweep(S, bstart[be], bstart[be + 1], own.x, own.y, rl, o, lst, cnt, a);
+                        sweep(S, bstart[be], bstart[be + 1], own.x, own.y, rl, o, lst, cnt, a.qx, a.qy);
                     }
                 }
                 if (a.nby >= 3) {
                     const int row = (by + 1 == a.nby ? 0 : by + 1) * a.nbx;
                     if (a.nbx < 3) {
-                        sweep(S, bstart[row], bstart[row + a.nbx], own.x, own.y, rl, o, lst, cnt, a);
+                        sweep(S, bstart[row], bstart[row + a.nbx], own.x, own.y, rl, o, lst, cnt, a.qx, a.qy);
                     } else if (bx == 0) {
-                        sweep(S, bstart[row], bstart[row + 2], own.x, own.y, rl, o, lst, cnt, a);
+                        sweep(S, bstart[row], bstart[row + 2], own.x, own.y, rl, o, lst, cnt, a.qx, a.qy);
                         sweep(S, bstart[row + a.nbx - 1], bstart[row + a.nbx], own.x, own.y, rl, o, lst,
-                              cnt, a);
+                              cnt, a.qx, a.qy);
                     } else if (bx == a.nbx - 1) {
                         sweep(S, bstart[row + a.nbx - 2], bstart[row + a.nbx], own.x, own.y, rl, o, lst,
-                              cnt, a);
-                        sweep(S, bstart[row], bstart[row + 1], own.x, own.y, rl, o, lst, cnt, a);
+                              cnt, a.qx, a.qy);
+                        sweep(S, bstart[row], bstart[row + 1], own.x, own.y, rl, o, lst, cnt, a.qx, a.qy);
                     } else {
                         sweep(S, bstart[row + bx - 1], bstart[row + bx + 2], own.x, own.y, rl, o, lst,
-                              cnt, a);
+                              cnt, a.qx, a.qy);
                     }
                 }
             }
@@ -806,15 +916,7 @@ __global__ __launch_bounds__(W >= 4 ? 64 * W : 256) void dem_step_kernel(StepArg
                 const float fy = (float)(int)(yl - 0x80000000u) * 2.3283064365386963e-10f;
                 double uo = a.u0, vo = a.v0, zeta = 0.0;
                 ocean_modes(fx, fy, mode_c[g], a.nmodes, a.modes.direct != 0, uo, vo, zeta);
-                const double du = uo - uld, dv = vo - vld;
-                const double sp = sqrt_nonneg(du * du + dv * dv);
-                const double alpha = a.cdrho * kPi * rld * rld;
-                fdx = alpha * du * sp;
-                fdy = alpha * dv * sp;
-                const double dW = 0.5 * zeta - wld;
-                const double r2 = rld * rld;
-                const double beta = a.cdrho * kPi * r2 * r2 * rld;
-                tdr = beta * dW * fabs(dW);
+                drag_terms(uo - uld, vo - vld, zeta, wld, rld, a.cdrho * kPi, fdx, fdy, tdr);
             }
             const double md = a.rho_ice_d * (double)vv.w * kPi * rld * rld;
 
@@ -979,7 +1081,9 @@ __global__ __launch_bounds__(W >= 4 ? 64 * W : 256) void dem_step_kernel(StepArg
 #pragma unroll
             for (int i = 0; i < SEG; ++i) x += src[16 * i];
             x = row_sum(x);
-            if (seg == 15 && valid) {
+            if (seg == 15 && valid && a.ring_slot && !wk.w) {
+                if (kq >= 3) a.ring_slot[(size_t)(kq - 3) * a.ncells + c] = kq < 5 ? (n > 0 ? x / (double)n : 0.0) : x;
+            } else if (seg == 15 && valid) {
                 const int slot = dyn_slot(kq);
                 double* const mo = wk.w ? a.mom_alt : a.mom;
                 mo[(size_t)c * kMomStride + slot] = x;
@@ -1030,14 +1134,7 @@ __global__ __launch_bounds__(256) void stats_kernel(StepArgs a, const int32_t* c
             const float fy = (float)(int)(yl - 0x80000000u) * 2.3283064365386963e-10f;
             double uo = a.u0, vo = a.v0, zeta = 0.0;
             ocean_modes(fx, fy, mode_c, a.nmodes, a.modes.direct != 0, uo, vo, zeta);
-            const double du = uo - uld, dv = vo - vld;
-            const double sp = sqrt_nonneg(du * du + dv * dv);
-            const double alpha = a.cdrho * kPi * rld * rld;
-            fdx = alpha * du * sp;
-            fdy = alpha * dv * sp;
-            const double dW = 0.5 * zeta - wld;
-            const double r2 = rld * rld;
-            tdr = a.cdrho * kPi * r2 * r2 * rld * dW * fabs(dW);
+            drag_terms(uo - uld, vo - vld, zeta, wld, rld, a.cdrho * kPi, fdx, fdy, tdr);
         }
         const double md = a.rho_ice_d * (double)a.h[s + l] * kPi * rld * rld;
         acc[M_N] += 1.0;
@@ -1070,13 +1167,13 @@ __global__ __launch_bounds__(256) void stats_kernel(StepArgs a, const int32_t* c
 }
 
 // ------------------------------------------------ standalone continuum step
-__global__ __launch_bounds__(64) void lf_kernel(const double* mom, const double* Q, double* Qn, int nx,
+__global__ __launch_bounds__(64) void lf_kernel(CellStats st, const double* Q, double* Qn, int nx,
                                                 int ny, double dT, double dX, double dY,
                                                 double inv_area, unsigned long long* max_cfl_bits,
                                                 uint32_t* err, int wall)
 {
     const int C = blockIdx.x * blockDim.x + threadIdx.x;
-    if (C < nx * ny) lf_cell(C, mom, Q, Qn, nx, ny, dT, dX, dY, inv_area, max_cfl_bits, err, wall != 0);
+    if (C < nx * ny) lf_cell(C, st, Q, Qn, nx, ny, dT, dX, dY, inv_area, max_cfl_bits, err, wall != 0);
 }
 
 // The same update for the listed cells only (the cells without floes, which
@@ -1087,7 +1184,7 @@ __global__ __launch_bounds__(64) void lf_list_kernel(const int32_t* cells, int n
                                                      uint32_t* err, int wall)
 {
     const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < ncl) lf_cell(cells[i], mom, Q, Qn, nx, ny, dT, dX, dY, inv_area, max_cfl_bits, err, wall != 0);
+    if (i < ncl) lf_cell(cells[i], stats_of_rows(mom), Q, Qn, nx, ny, dT, dX, dY, inv_area, max_cfl_bits, err, wall != 0);
 }
 
 __global__ void q_from_moments_kernel(const double* mom, double* Q, int nc, double inv_area)

@@ -147,7 +147,7 @@ __global__ __launch_bounds__(64) void resync_kernel(const int32_t* cells, const 
 // state, T: the network's residual tendency, applied while the cell's reduced
 // DEM is younger than `window`, always if window <= 0), the others the LF
 // step of their statistics.
-__global__ void hybrid_continuum_kernel(const double* mom, const double* Q, const double* Qb, double* Qn,
+__global__ void hybrid_continuum_kernel(CellStats st, const double* Q, const double* Qb, double* Qn,
                                         const int32_t* row, const float* T, const double* red, double t,
                                         double window, int nx, int ny, double dT, double dX, double dY,
                                         double inv_area, unsigned long long* max_cfl_bits, uint32_t* err)
@@ -161,14 +161,14 @@ __global__ void hybrid_continuum_kernel(const double* mom, const double* Q, cons
 #pragma unroll
         for (int f = 0; f < 4; ++f) Qn[(size_t)f * nc + C] = Qb[(size_t)f * nc + C] + w * (double)T[(size_t)q * 4 + f];
     } else {
-        lf_cell(C, mom, Q, Qn, nx, ny, dT, dX, dY, inv_area, max_cfl_bits, err, false);   // the hybrid has no walls
+        lf_cell(C, st, Q, Qn, nx, ny, dT, dX, dY, inv_area, max_cfl_bits, err, false);   // the hybrid has no walls
     }
 }
 
 // Plain-method residual tendency (LF(Q) - Qb) / dT of the listed cells: their
 // own coefficients and sources from the statistics `fresh`, the neighbours'
-// coefficients from `mom`.
-__global__ void check_tendency_kernel(const int32_t* cells, int ncl, const double* fresh, const double* mom,
+// coefficients from `st`.
+__global__ void check_tendency_kernel(const int32_t* cells, int ncl, const double* fresh, CellStats st,
                                       const double* Q, const double* Qb, int nx, int ny, double dT, double dX,
                                       double dY, double inv_area, float* T)
 {
@@ -183,10 +183,10 @@ __global__ void check_tendency_kernel(const int32_t* cells, int ncl, const doubl
     const int S = (iy == 0 ? ny - 1 : iy - 1) * nx + ix;
     const double* sC = fresh + (size_t)C * kMomStride;
     const double uC = sC[M_UBAR], vC = sC[M_VBAR];
-    const double uE = E == C ? uC : mom[(size_t)E * kMomStride + M_UBAR];
-    const double uW = W == C ? uC : mom[(size_t)W * kMomStride + M_UBAR];
-    const double vN = N == C ? vC : mom[(size_t)N * kMomStride + M_VBAR];
-    const double vS = S == C ? vC : mom[(size_t)S * kMomStride + M_VBAR];
+    const double uE = E == C ? uC : st.ub[(size_t)E * st.stride];
+    const double uW = W == C ? uC : st.ub[(size_t)W * st.stride];
+    const double vN = N == C ? vC : st.vb[(size_t)N * st.stride];
+    const double vS = S == C ? vC : st.vb[(size_t)S * st.stride];
     const double cx = dT / (2.0 * dX), cy = dT / (2.0 * dY);
     for (int f = 0; f < 4; ++f) {
         const double qE = Q[(size_t)f * nc + E], qW = Q[(size_t)f * nc + W];
@@ -218,7 +218,7 @@ struct HybridState {
     double tol = 0.2;
     double net_window = 0.0;              // seconds after a reduced DEM's start the network acts (<= 0: always)
     int64_t checks = 0, fallbacks = 0, cursor = 0, hsteps = 0;
-    const double* last_mom = nullptr;     // statistics of the step just taken (the block ring, or momb)
+    CellStats last = {};                  // statistics of the step just taken (the block ring, or momb)
     Bucket bk[kNumBuckets];               // DEM-mode cells, and the pool's closure-mode cells (shadow DEM:
                                           // their statistics go to scratch)
     std::vector<int32_t> clos_h;          // closure-mode cells
@@ -373,8 +373,8 @@ sp_status hybrid_check(sp_ctx* c, double dt)
                        h->Qs, ca, dt);
     HIP_TRY(c, hipGetLastError());
     hipLaunchKernelGGL(check_tendency_kernel, dim3((nk + 63) / 64), dim3(64), 0, c->stream, h->chk_d, nk, c->mom2,
-                       h->last_mom ? h->last_mom : c->momb[k & 1], c->Q[c->kstep & 1], h->Qs, c->p.nx, c->p.ny, dt, c->p.cell_lx, c->p.cell_ly,
-                       inv_area, h->Tdem);
+                       h->last.ub ? h->last : stats_of_rows(c->momb[k & 1]), c->Q[c->kstep & 1], h->Qs, c->p.nx, c->p.ny,
+                       dt, c->p.cell_lx, c->p.cell_ly, inv_area, h->Tdem);
     HIP_TRY(c, hipGetLastError());
     // 3. the closure's residual for the same cells
     hipLaunchKernelGGL(features_kernel, dim3((nk + 63) / 64), dim3(64), 0, c->stream, h->chk_d, nk, h->Qs, ca,
@@ -531,7 +531,6 @@ sp_status sp_hybrid_set(sp_ctx* c, sp_mlp* net, const uint8_t* closure_cells, in
     for (int q = 0; q < kNumBuckets; ++q) {
         h->bk[q].waves = c->bk[q].waves;
         h->bk[q].persist = c->bk[q].persist;
-        h->bk[q].bwaves = c->bk[q].bwaves;
     }
     const size_t nk = (size_t)std::max(1, check_cells);
     SP_TRY(dalloc(c, &h->row_d, (size_t)c->ncells));
@@ -568,7 +567,7 @@ sp_status sp_step_hybrid(sp_ctx* c, double dt, int64_t nsteps)
     StepArgs base = make_args(c, dt);
     base.mom_alt = c->mom2;
     const double inv_area = 1.0 / (c->p.cell_lx * c->p.cell_ly);
-    const size_t slot = (size_t)c->ncells * kMomStride;
+    const size_t slot = (size_t)c->ncells * kRing;
     // The DEM cells never read the continuum between checks (no coarse-to-fine
     // update at this cadence), so their steps up to the next check or the end
     // of a fallback window run as blocked launches (statistics of step t into
@@ -635,15 +634,15 @@ sp_status sp_step_hybrid(sp_ctx* c, double dt, int64_t nsteps)
         }
         for (int64_t t = 0; t < K; ++t, ++it) {
             const int64_t k = c->kstep;
-            double* const mom = ring ? ring + (size_t)t * slot : c->momb[k & 1];
+            const CellStats st = ring ? stats_of_slot(ring + (size_t)t * slot, c->ncells) : stats_of_rows(c->momb[k & 1]);
             const int nclos = (int)h->clos_h.size();
             if (nclos > 0) {
                 // base-updated level-k state, the network's residual for its
                 // features, the closure cells' coefficients from their reduced DEMs
                 ClosureArgs ca = closure_args(c, c->t_now);
-                // (the closure cells' <v> go into this step's statistics row as well)
+                // (the closure cells' <v> go into this step's statistics as well)
                 hipLaunchKernelGGL(reduced_stats_kernel, dim3((c->ncells + 255) / 256), dim3(256), 0, c->stream, ca,
-                                   h->rs, h->row_d, mom);
+                                   h->rs, h->row_d, const_cast<double*>(st.ub), const_cast<double*>(st.vb), st.stride);
                 HIP_TRY(c, hipGetLastError());
                 ca.rs = h->rs;   // every cell's reduced statistics once, read by the stencils below
                 hipLaunchKernelGGL(base_kernel, dim3((c->ncells + 127) / 128), dim3(128), 0, c->stream, c->Q[k & 1],
@@ -659,12 +658,12 @@ sp_status sp_step_hybrid(sp_ctx* c, double dt, int64_t nsteps)
             // drives them); in a block, already done
             if (!ring)
                 for (auto& b : h->bk) SP_TRY(launch_bucket(c, b, base, k, false));
-            hipLaunchKernelGGL(hybrid_continuum_kernel, dim3((c->ncells + 127) / 128), dim3(128), 0, c->stream, mom,
+            hipLaunchKernelGGL(hybrid_continuum_kernel, dim3((c->ncells + 127) / 128), dim3(128), 0, c->stream, st,
                                c->Q[k & 1], h->Qs, c->Q[(k + 1) & 1], h->row_d, h->T, c->red, c->t_now,
                                h->net_window, c->p.nx, c->p.ny, dt, c->p.cell_lx, c->p.cell_ly, inv_area,
                                c->cfl_bits_d, c->err_d);
             HIP_TRY(c, hipGetLastError());
-            h->last_mom = mom;
+            h->last = st;
             c->kstep++;
             c->steps++;
             c->t_now += dt;

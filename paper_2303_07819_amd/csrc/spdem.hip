@@ -46,15 +46,21 @@ constexpr int kDefaultWaves[kNumBuckets] = {1, 2, 4, 4, 8};
 constexpr int kDefaultGraphChunk = 16;
 constexpr int kDefaultStepBlock = 32;   // steps per blocked DEM launch
 
+// A run of a bucket's cells that one blocked launch takes: the wavefronts that
+// hold one floe per lane of its largest cell, and that cell's floes rounded up.
+struct Segment {
+    int first, count, waves, cap;
+};
+
 struct Bucket {
     int waves = 4;
     int persist = 0;                    // resident workgroups stride over the cells
-    int bwaves = 0;                     // wavefronts per cell of blocked launches (0: derived from waves)
     int cap = 0;                        // LDS floe capacity per group
     int resident = 1;                   // workgroups resident at once (persistent grid size)
     std::vector<int32_t> cells_h;       // costliest first
     int4* work_d = nullptr;             // (cell, first floe, count, -) per entry of cells_h
     size_t work_cap = 0;                // entries work_d holds
+    std::vector<Segment> segs;          // blocked launches of the bucket
 };
 
 }  // namespace
@@ -96,6 +102,7 @@ struct sp_ctx {
     float *u = nullptr, *v = nullptr, *w = nullptr, *th = nullptr, *r = nullptr, *h = nullptr;
     int32_t* cell_start = nullptr;
     double2* phase = nullptr;
+    ModeC* modec = nullptr;                 // [ncells][nmodes]: mode constants of every cell (blocked launches)
     double* ocen = nullptr;                 // [ncells][4]: ocean u, v and curl at each cell centre, 0
     double* momb[2] = {nullptr, nullptr};   // statistics of time level k in momb[k & 1]
     double* mom2 = nullptr;                 // statistics of the current state (read_moments)
@@ -127,9 +134,9 @@ struct sp_ctx {
     int32_t N0 = 1, N1 = 1, n_t = 1;
     int64_t cpl_j = 0;                      // fine steps since the cadence was set
     int64_t cpl_nudges = 0;                 // coarse-to-fine update passes since then
-    double* cpl_ring = nullptr;             // [N0][ncells][kMomStride] window statistics
+    double* cpl_ring = nullptr;             // [N0][kRing][ncells] window statistics
     int32_t cpl_ring_slots = 0;
-    double* cpl_mean = nullptr;             // [ncells][kMomStride] mean of the window
+    double* cpl_mean = nullptr;             // [kRing][ncells] mean of the window
     double* cpl_x0 = nullptr;               // [ncells][kMomStride] statistics at the coarse-step start
     int32_t* cpl_cells = nullptr;           // cells with floes
     int32_t cpl_ncl = 0;
@@ -139,7 +146,7 @@ struct sp_ctx {
 
     // temporal blocking of the plain step: K steps per DEM launch (1: per step)
     int32_t block_k = kDefaultStepBlock;
-    double* blk_ring = nullptr;             // [2][block_k][ncells][kMomStride] statistics of two blocks' steps
+    double* blk_ring = nullptr;             // [2][block_k][kRing][ncells] statistics of two blocks' steps
     int32_t blk_ring_slots = 0;
     int blk_parity = 0;                     // ring half of the next block
     hipStream_t lf_stream = nullptr;        // continuum updates of blocks (default priority)
@@ -271,7 +278,7 @@ void free_all(sp_ctx* c)
     drop_graph(c);
     hybrid_free(c);
     coupling_free(c);
-    void* ps[] = {c->xi, c->yi, c->u, c->v, c->w, c->th, c->r, c->h, c->cell_start, c->phase, c->ocen,
+    void* ps[] = {c->xi, c->yi, c->u, c->v, c->w, c->th, c->r, c->h, c->cell_start, c->phase, c->modec, c->ocen,
                   c->momb[0], c->momb[1], c->mom2, c->Q[0], c->Q[1], c->err_d, c->contacts_d,
                   c->cfl_bits_d, c->desc, c->mf, c->red, c->qprev, c->vlist, c->vcount, c->vdisp, c->empty_d,
                   c->blk_ring, c->cands_d, c->tsp_j, c->tsp_x};
@@ -285,6 +292,7 @@ void free_all(sp_ctx* c)
     c->u = c->v = c->w = c->th = c->r = c->h = nullptr;
     c->cell_start = nullptr;
     c->phase = nullptr;
+    c->modec = nullptr;
     c->ocen = nullptr;
     c->momb[0] = c->momb[1] = c->mom2 = nullptr;
     c->Q[0] = c->Q[1] = nullptr;
@@ -340,6 +348,7 @@ StepArgs make_args(const sp_ctx* c, double dt)
     a.h = c->h;
     a.cell_start = c->cell_start;
     a.phase = c->phase;
+    a.modec = c->modec;
     a.vlist = c->vlist;
     a.vcount = c->vcount;
     a.tsp_j = c->tsp_j;
@@ -408,6 +417,12 @@ sp_status upload_phase(sp_ctx* c)
     SP_TRY(dalloc(c, &c->phase, tab.size()));
     HIP_TRY(c, hipMemcpyAsync(c->phase, tab.data(), tab.size() * sizeof(double2), hipMemcpyHostToDevice,
                               c->stream));
+    SP_TRY(dalloc(c, &c->modec, tab.size()));
+    if (c->nmodes > 0) {
+        hipLaunchKernelGGL(mode_table_kernel, dim3((unsigned)((tab.size() + 255) / 256)), dim3(256), 0, c->stream,
+                           c->ncells, c->nmodes, make_args(c, 0.0).modes, c->phase, c->modec);
+        HIP_TRY(c, hipGetLastError());
+    }
     SP_TRY(upload_ocean_centres(c));
     HIP_TRY(c, hipStreamSynchronize(c->stream));
     c->phase_dirty = false;
@@ -510,37 +525,33 @@ sp_status prepare_sel(sp_ctx* c, int sched, int waves, int persist, int threads,
 }
 
 template <int SCHED, int W, bool TSP>
-sp_status launch_block_tt(sp_ctx* c, hipStream_t st, const StepArgs& a, int grid, int threads, size_t lds, int K,
-                          const BlockNudge& nd)
+sp_status launch_block_tt(sp_ctx* c, hipStream_t st, const BlockArgs& a, int grid, int threads, size_t lds)
 {
     if (lds > 65536)
         HIP_TRY(c, hipFuncSetAttribute((const void*)dem_block_kernel<SCHED, W, TSP>,
                                        hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
-    hipLaunchKernelGGL((dem_block_kernel<SCHED, W, TSP>), dim3(grid), dim3(threads), lds, st, a, K, nd);
+    hipLaunchKernelGGL((dem_block_kernel<SCHED, W, TSP>), dim3(grid), dim3(threads), lds, st, a);
     HIP_TRY(c, hipGetLastError());
     return SP_OK;
 }
 
 template <int SCHED, int W>
-sp_status launch_block_t(sp_ctx* c, hipStream_t st, const StepArgs& a, int grid, int threads, size_t lds, int K,
-                         const BlockNudge& nd)
+sp_status launch_block_t(sp_ctx* c, hipStream_t st, const BlockArgs& a, int grid, int threads, size_t lds)
 {
-    if (a.flags & SP_TANGENTIAL_SPRING) return launch_block_tt<SCHED, W, true>(c, st, a, grid, threads, lds, K, nd);
-    return launch_block_tt<SCHED, W, false>(c, st, a, grid, threads, lds, K, nd);
+    if (a.flags & SP_TANGENTIAL_SPRING) return launch_block_tt<SCHED, W, true>(c, st, a, grid, threads, lds);
+    return launch_block_tt<SCHED, W, false>(c, st, a, grid, threads, lds);
 }
 
-sp_status launch_block_sel(sp_ctx* c, hipStream_t st, int sched, int waves, const StepArgs& a, int grid,
-                           int threads, size_t lds, int K, const BlockNudge& nd)
+sp_status launch_block_sel(sp_ctx* c, hipStream_t st, int sched, int waves, const BlockArgs& a, int grid,
+                           int threads, size_t lds)
 {
     const bool binned = sched == SP_SCHED_BINNED;
-    switch (waves) {
-    case 1: return binned ? launch_block_t<2, 1>(c, st, a, grid, threads, lds, K, nd) : launch_block_t<1, 1>(c, st, a, grid, threads, lds, K, nd);
-    case 2: return binned ? launch_block_t<2, 2>(c, st, a, grid, threads, lds, K, nd) : launch_block_t<1, 2>(c, st, a, grid, threads, lds, K, nd);
-    case 4: return binned ? launch_block_t<2, 4>(c, st, a, grid, threads, lds, K, nd) : launch_block_t<1, 4>(c, st, a, grid, threads, lds, K, nd);
-    case 8: return binned ? launch_block_t<2, 8>(c, st, a, grid, threads, lds, K, nd) : launch_block_t<1, 8>(c, st, a, grid, threads, lds, K, nd);
-    case 16: return binned ? launch_block_t<2, 16>(c, st, a, grid, threads, lds, K, nd) : launch_block_t<1, 16>(c, st, a, grid, threads, lds, K, nd);
-    default: return fail(c, SP_EINVAL, "no blocked kernel for waves=%d", waves);
-    }
+    if (waves < 1 || waves > 16) return fail(c, SP_EINVAL, "no blocked kernel for waves=%d", waves);
+    if (waves <= 4)
+        return binned ? launch_block_t<2, 4>(c, st, a, grid, threads, lds) : launch_block_t<1, 4>(c, st, a, grid, threads, lds);
+    if (waves <= 8)
+        return binned ? launch_block_t<2, 8>(c, st, a, grid, threads, lds) : launch_block_t<1, 8>(c, st, a, grid, threads, lds);
+    return binned ? launch_block_t<2, 16>(c, st, a, grid, threads, lds) : launch_block_t<1, 16>(c, st, a, grid, threads, lds);
 }
 
 size_t bucket_group_bytes(const sp_ctx* c, const Bucket& b)
@@ -562,7 +573,7 @@ sp_status prepare_bucket(sp_ctx* c, Bucket& b)
 // One DEM launch for bucket b at time level k (writes the statistics of level
 // k); with lf, the continuum update of level k - 1 runs in the same launch.
 // `fixed` (autotuning) supplies every buffer pointer itself; mom_to (coupled
-// cadence) takes the statistics instead, with no continuum update.
+// cadence, one slot of its ring) takes the statistics instead, with no continuum update.
 sp_status launch_bucket(sp_ctx* c, const Bucket& b, const StepArgs& base, int64_t k, bool lf,
                         bool fixed = false, double* mom_to = nullptr)
 {
@@ -579,7 +590,7 @@ sp_status launch_bucket(sp_ctx* c, const Bucket& b, const StepArgs& base, int64_
         a.Qp = c->Q[(k + 1) & 1];
         a.Qn = c->Q[k & 1];
         if (mom_to) {
-            a.mom = mom_to;
+            a.ring_slot = mom_to;
             a.lf = 0;
         }
     }
@@ -591,55 +602,123 @@ sp_status launch_bucket(sp_ctx* c, const Bucket& b, const StepArgs& base, int64_
     return launch_sel(c, c->sched, b.waves, persist, a, grid, bucket_threads(c, b), bucket_lds(c, b));
 }
 
-// Wavefronts per cell of a bucket's blocked launches: the autotuner's choice
-// where it made one, else the bucket's own W when its cells have at most 64 W
-// floes, else the smallest of 8 and 16 that holds one floe per lane (up to the
+// Upper limit of the wavefronts per cell of a bucket's blocked launches, which
+// take one per 64 floes: the bucket's own W when its cells have at most 64 W
+// floes, else the smaller of 8 and 16 that holds one floe per lane (up to the
 // 1024-floe cell limit).
 int block_waves(const Bucket& b)
 {
-    if (b.bwaves > 0 && b.cap <= 64 * b.bwaves) return b.bwaves;
     if (b.cap <= 64 * b.waves) return b.waves;
     return b.cap <= 512 ? 8 : 16;
 }
 
-// LDS of one cell of a blocked launch: the per-step layout, 1 / m and
-// 1 / (m r^2) per floe beside the state, and with the tangential spring the
-// floes' contact history.
+// LDS of one cell of a blocked launch: per floe its position and radius, its
+// velocity (16 B each; the sorted copy of a binned search lies over the
+// velocities), its candidates and their count; the sub-bins of a binned search;
+// with the tangential spring the floes' contact history.
 constexpr size_t kBlockLdsMax = 160 * 1024;
+constexpr int kMaxBlockWaves = SP_MAX_CELL_FLOES / 64;
+// A launch of fewer steps than this takes a bucket's runs together: its time is
+// its launches and reads, not the wavefronts that a cell has too many (a
+// sampling step of 64 x 64 cells of 0 to 700 floes takes 95 us with the runs
+// together, 105 apart; 32 steps of 128 x 128 such cells 2670 us apart, 2750
+// together).
+constexpr int kRunSteps = 4;
 
-size_t block_group_bytes(const sp_ctx* c, int cap, int waves)
+size_t block_cell_bytes(const sp_ctx* c, int cap)
 {
-    size_t b = group_bytes(c->sched, cap, c->nbx * c->nby, waves) + (size_t)cap * 16;
+    size_t b = (size_t)cap * (16 + 16 + 2 * kListCap + 4);
+    if (c->sched == SP_SCHED_BINNED) b += (size_t)(2 * c->nbx * c->nby + 1) * 4;
+    b = (b + 15) & ~(size_t)15;
     if (c->p.flags & SP_TANGENTIAL_SPRING) b += (size_t)cap * kSpringBytes;
     return b;
 }
 
+// The arguments of a blocked launch that do not depend on the bucket, from the
+// step arguments.
+BlockArgs block_args_of(const StepArgs& a, double* ring, int K, const BlockNudge& nd)
+{
+    BlockArgs b;
+    memset(&b, 0, sizeof b);
+    b.xi = a.xi;
+    b.yi = a.yi;
+    b.u = a.u;
+    b.v = a.v;
+    b.w = a.w;
+    b.th = a.th;
+    b.r = const_cast<float*>(a.r);
+    b.h = a.h;
+    b.modes = a.modec;
+    b.tsp_j = a.tsp_j;
+    b.tsp_x = a.tsp_x;
+    b.vlist = a.vlist;
+    b.vcount = a.vcount;
+    b.vdisp = a.vdisp;
+    b.contacts = a.contacts;
+    b.cands = a.cands;
+    b.err = a.err;
+    b.ring = ring;
+    b.alt = a.mom_alt;
+    b.ncells = a.ncells;
+    b.K = K;
+    b.nmodes = a.nmodes;
+    b.nbx = a.nbx;
+    b.nby = a.nby;
+    b.flags = a.flags;
+    b.skin = a.skin;
+    b.qx = a.qx;
+    b.qy = a.qy;
+    b.inv_qx = (float)a.inv_qxd;
+    b.ratio = (float)(a.qyd / a.qxd);
+    b.qxd = a.qxd;
+    b.qyd = a.qyd;
+    b.inv_qxd = a.inv_qxd;
+    b.inv_qyd = a.inv_qyd;
+    b.dtd = a.dtd;
+    b.Ed = a.Ed;
+    b.Gd = a.Gd;
+    b.mud = a.mud;
+    b.cdpi = a.cdrho * kPi;
+    b.rho_ice_d = a.rho_ice_d;
+    b.u0 = a.u0;
+    b.v0 = a.v0;
+    b.direct = a.modes.direct;
+    b.nd = nd;
+    return b;
+}
+
 // K steps from level kstep as one blocked launch per bucket (of bk, default the
-// context's buckets), the statistics of step t into mom + t * (ncells x
-// kMomStride) (work entries flagged for mom_alt: there); with an active nd, the
+// context's buckets), the statistics of step t into slot t of ring (kRing x
+// ncells each; work entries flagged for mom_alt: there); with an active nd, the
 // coarse-to-fine update of every launched cell at the end.
-sp_status launch_blocks(sp_ctx* c, const StepArgs& base, double* mom, int K, const BlockNudge& nd,
+sp_status launch_blocks(sp_ctx* c, const StepArgs& base, double* ring, int K, const BlockNudge& nd,
                         const Bucket* bk = nullptr, hipStream_t on = nullptr)
 {
     if (!bk) bk = c->bk;
     const hipStream_t s0 = on ? on : c->stream;   // the stream the launches follow and that waits for them
-    // with several buckets, the one of most floes on the library stream and
-    // the others beside it on a second stream (their cells are disjoint; the
-    // library stream waits for both)
-    int main_q = -1, nb = 0;
-    int64_t most = -1;
+    // with several launches, dealt to the library stream and a second one,
+    // largest first, each to the stream with less to do (their cells are
+    // disjoint; the library stream waits for both)
+    struct Launch {
+        const Bucket* b;
+        Segment s;
+        int64_t cost;
+    };
+    Launch todo[kMaxBlockWaves];   // at most one run per number of wavefronts
+    size_t nb = 0;
     for (int q = 0; q < kNumBuckets; ++q) {   // every bucket checked before any launch
         const Bucket& b = bk[q];
         if (b.cells_h.empty()) continue;
-        const int w = block_waves(b);
-        if (b.cap > 64 * w) return fail(c, SP_EINVAL, "%d floes per cell exceed a blocked launch", b.cap);
-        if (block_group_bytes(c, b.cap, w) > kBlockLdsMax)
+        if (block_cell_bytes(c, b.cap) > kBlockLdsMax)
             return fail(c, SP_ECAPACITY, "%d floes per cell exceed the LDS of a blocked launch", b.cap);
-        ++nb;
-        const int64_t f = (int64_t)bk[q].cells_h.size() * bk[q].cap;
-        if (f > most) {
-            most = f;
-            main_q = q;
+        const size_t runs = K >= kRunSteps ? b.segs.size() : 1;
+        for (size_t g = 0; g < runs; ++g) {
+            Segment s = b.segs[g];
+            if (runs == 1) s.count = (int)b.cells_h.size();
+            const Launch l = {&b, s, (int64_t)s.count * s.waves};
+            size_t i = nb++;
+            for (; i > 0 && todo[i - 1].cost < l.cost; --i) todo[i] = todo[i - 1];
+            todo[i] = l;
         }
     }
     if (nb > 1) {
@@ -652,22 +731,17 @@ sp_status launch_blocks(sp_ctx* c, const StepArgs& base, double* mom, int K, con
         HIP_TRY(c, hipStreamWaitEvent(c->bk_stream, c->bk_fork, 0));
     }
     sp_status status = SP_OK;
-    for (int q = 0; q < kNumBuckets; ++q) {
-        const Bucket& b = bk[q];
-        if (b.cells_h.empty()) continue;
-        const hipStream_t st = (nb > 1 && q != main_q) ? c->bk_stream : s0;
-        const int w = block_waves(b);
-        const size_t gbytes = block_group_bytes(c, b.cap, w);
-        const int gpb = groups_per_block(w, gbytes);
-        StepArgs a = base;
-        a.work = b.work_d;
-        a.ncl = (int32_t)b.cells_h.size();
-        a.cap = b.cap;
-        a.group_bytes = (int32_t)gbytes;
-        a.mom = mom;
-        a.lf = 0;
-        const int grid = (int)((b.cells_h.size() + gpb - 1) / gpb);
-        status = launch_block_sel(c, st, c->sched, w, a, grid, gpb * 64 * w, (size_t)gpb * gbytes, K, nd);
+    BlockArgs a = block_args_of(base, ring, K, nd);
+    int64_t load[2] = {0, 0};
+    for (size_t i = 0; i < nb; ++i) {
+        const Launch& l = todo[i];
+        const int on2 = load[1] < load[0] ? 1 : 0;
+        load[on2] += l.cost;
+        const size_t bytes = block_cell_bytes(c, l.s.cap);
+        a.work = l.b->work_d + l.s.first;
+        a.cap = l.s.cap;
+        a.cell_bytes = (int32_t)bytes;
+        status = launch_block_sel(c, on2 ? c->bk_stream : s0, c->sched, l.s.waves, a, l.s.count, 64 * l.s.waves, bytes);
         if (status) break;
     }
     if (nb > 1) {   // joined also after a failed launch: nothing stays behind on the second stream
@@ -696,7 +770,7 @@ sp_status flush_lf(sp_ctx* c)
 {
     if (!c->lf_pending) return SP_OK;
     const int64_t k = c->kstep - 1;
-    hipLaunchKernelGGL(lf_kernel, dim3((c->ncells + 63) / 64), dim3(64), 0, c->stream, c->momb[k & 1],
+    hipLaunchKernelGGL(lf_kernel, dim3((c->ncells + 63) / 64), dim3(64), 0, c->stream, stats_of_rows(c->momb[k & 1]),
                        c->Q[k & 1], c->Q[(k + 1) & 1], c->p.nx, c->p.ny, c->lf_dt, c->p.cell_lx,
                        c->p.cell_ly, 1.0 / (c->p.cell_lx * c->p.cell_ly), c->cfl_bits_d, c->err_d, wall_x(c));
     HIP_TRY(c, hipGetLastError());
@@ -712,7 +786,7 @@ bool block_eligible(const sp_ctx* c)
     // with the tangential spring, while every bucket's cells fit a blocked launch's LDS
     if (c->p.flags & SP_TANGENTIAL_SPRING)
         for (const auto& b : c->bk)
-            if (!b.cells_h.empty() && block_group_bytes(c, b.cap, block_waves(b)) > kBlockLdsMax) return false;
+            if (!b.cells_h.empty() && block_cell_bytes(c, b.cap) > kBlockLdsMax) return false;
     return true;
 }
 
@@ -732,7 +806,7 @@ sp_status join_block_lf(sp_ctx* c)
 sp_status block_prepare(sp_ctx* c)
 {
     const int K = c->block_k;
-    const size_t slot = (size_t)c->ncells * kMomStride;
+    const size_t slot = (size_t)c->ncells * kRing;
     if (!c->blk_ring || c->blk_ring_slots != K) {
         SP_TRY(join_block_lf(c));
         HIP_TRY(c, hipStreamSynchronize(c->stream));
@@ -761,7 +835,7 @@ sp_status block_prepare(sp_ctx* c)
 sp_status block_chunk(sp_ctx* c, const StepArgs& base, int K, bool time_dem = false, hipEvent_t e0 = nullptr,
                       hipEvent_t e1 = nullptr)
 {
-    const size_t slot = (size_t)c->ncells * kMomStride;
+    const size_t slot = (size_t)c->ncells * kRing;
     SP_TRY(block_prepare(c));
     if (K < 1 || K > c->blk_ring_slots) return fail(c, SP_EINVAL, "block of %d steps outside [1, %d]", K, c->blk_ring_slots);
     SP_TRY(flush_lf(c));
@@ -780,7 +854,8 @@ sp_status block_chunk(sp_ctx* c, const StepArgs& base, int K, bool time_dem = fa
         HIP_TRY(c, hipStreamWaitEvent(c->lf_stream, c->dem_done[r], 0));
         for (int t = 0; t < K; ++t) {
             const int64_t k = c->kstep + t;
-            hipLaunchKernelGGL(lf_kernel, dim3((c->ncells + 63) / 64), dim3(64), 0, c->lf_stream, ring + t * slot,
+            hipLaunchKernelGGL(lf_kernel, dim3((c->ncells + 63) / 64), dim3(64), 0, c->lf_stream,
+                               stats_of_slot(ring + t * slot, c->ncells),
                                c->Q[k & 1], c->Q[(k + 1) & 1], c->p.nx, c->p.ny, base.dtd, c->p.cell_lx,
                                c->p.cell_ly, base.inv_area, c->cfl_bits_d, c->err_d, wall_x(c));
             HIP_TRY(c, hipGetLastError());
@@ -806,6 +881,23 @@ sp_status prepare_buckets(sp_ctx* c)
     return SP_OK;
 }
 
+// Blocked launches of a bucket: its cells (most floes first) in runs of one
+// number of wavefronts, except that a run shorter than kSegmentCells (about one
+// cell per compute unit: a launch that would leave most of the chip idle) takes
+// the cells after it as well.
+constexpr int kSegmentCells = 256;
+
+void make_segments(Bucket& b, const int32_t* counts)
+{
+    b.segs.clear();
+    for (size_t i = 0; i < b.cells_h.size(); ++i) {
+        const int n = counts[b.cells_h[i]], w = std::max(1, (n + 63) / 64);
+        if (b.segs.empty() || (w < b.segs.back().waves && b.segs.back().count >= kSegmentCells))
+            b.segs.push_back({(int)i, 0, w, std::max(16, (n + 15) / 16 * 16)});
+        ++b.segs.back().count;
+    }
+}
+
 // Count buckets over the cells with include[cell] != 0 (all cells if null),
 // costliest first (the order fixed when the floes were set); counts must be
 // the context's counts.  alt (per cell, may be null): 1 sends a cell's
@@ -826,6 +918,7 @@ sp_status build_buckets_into(sp_ctx* c, Bucket* bk, const int32_t* counts, const
         int mx = 0;
         for (int32_t cell : b.cells_h) mx = std::max(mx, counts[cell]);
         b.cap = std::max(16, (mx + 15) / 16 * 16);
+        make_segments(b, counts);
         work[q].resize(b.cells_h.size());
         for (size_t i = 0; i < work[q].size(); ++i) {
             const int32_t cell = b.cells_h[i];
@@ -945,27 +1038,26 @@ sp_status capture_graph(sp_ctx* c, double dt)
 }
 
 // Autotuning of blocked steps on a scratch copy of the state (`a` points at
-// it): every non-empty bucket alone, over the wavefronts per cell that hold one
-// floe per lane (W = 1 .. 16), then the block length over the whole step
-// (16, 32, 64 steps); each variant one warm-up launch and the minimum of reps
-// timed launches, per step.  Sets each bucket's bwaves and the block length.
+// it): the block length over the whole step (16, 32, 64 steps; the wavefronts
+// of a cell follow from its floes), each one warm-up launch and the minimum of
+// reps timed launches, per step.
 constexpr int kTuneBlocks[3] = {16, 32, 64};
 
 sp_status tune_blocked(sp_ctx* c, StepArgs a, int reps, hipEvent_t e0, hipEvent_t e1, double* total)
 {
     double* smom = nullptr;
     unsigned long long* scands = nullptr;
-    sp_status st = dalloc(c, &smom, (size_t)kTuneBlocks[2] * c->ncells * kMomStride);
+    sp_status st = dalloc(c, &smom, (size_t)kTuneBlocks[2] * c->ncells * kRing);
     if (!st) st = dalloc(c, &scands, std::max<size_t>(1, (size_t)c->ncells));
     a.cands = scands;
     BlockNudge none;
     memset(&none, 0, sizeof none);
-    auto time_blocks = [&](const Bucket* bk, int K, double* per_step) -> sp_status {
-        SP_TRY(launch_blocks(c, a, smom, K, none, bk));   // warm-up (and list rebuilds)
+    auto time_blocks = [&](int K, double* per_step) -> sp_status {
+        SP_TRY(launch_blocks(c, a, smom, K, none));   // warm-up (and list rebuilds)
         double best = 1e30;
         for (int r = 0; r < reps; ++r) {
             HIP_TRY(c, hipEventRecord(e0, c->stream));
-            SP_TRY(launch_blocks(c, a, smom, K, none, bk));
+            SP_TRY(launch_blocks(c, a, smom, K, none));
             HIP_TRY(c, hipEventRecord(e1, c->stream));
             HIP_TRY(c, hipEventSynchronize(e1));
             float ms = 0.0f;
@@ -975,39 +1067,11 @@ sp_status tune_blocked(sp_ctx* c, StepArgs a, int reps, hipEvent_t e0, hipEvent_
         *per_step = best;
         return SP_OK;
     };
-    const int wv[5] = {1, 2, 4, 8, 16};
-    double sum = 0.0;
-    for (int q = 0; q < kNumBuckets && !st; ++q) {
-        Bucket& b = c->bk[q];
-        if (b.cells_h.empty()) continue;
-        Bucket trial[kNumBuckets];
-        trial[q].cap = b.cap;
-        trial[q].waves = b.waves;
-        trial[q].cells_h = b.cells_h;
-        trial[q].work_d = b.work_d;
-        double best = 1e30;
-        int bw = block_waves(b);
-        for (int wi = 0; wi < 5 && !st; ++wi) {
-            if (b.cap > 64 * wv[wi]) continue;        // one floe per lane
-            trial[q].bwaves = wv[wi];
-            double t = 0.0;
-            st = time_blocks(trial, c->block_k, &t);
-            if (!st && t < best) {
-                best = t;
-                bw = wv[wi];
-            }
-        }
-        trial[q].work_d = nullptr;    // owned by the real bucket
-        if (!st) {
-            b.bwaves = bw;
-            sum += best;
-        }
-    }
     int bestK = c->block_k;
     double bestT = 1e30;
     for (int i = 0; i < 3 && !st; ++i) {
         double t = 0.0;
-        st = time_blocks(c->bk, kTuneBlocks[i], &t);
+        st = time_blocks(kTuneBlocks[i], &t);
         if (!st && t < bestT) {
             bestT = t;
             bestK = kTuneBlocks[i];
@@ -1018,7 +1082,7 @@ sp_status tune_blocked(sp_ctx* c, StepArgs a, int reps, hipEvent_t e0, hipEvent_
     if (scands) (void)hipFree(scands);
     if (st) return st;
     c->block_k = bestK;
-    *total = bestT < 1e30 ? bestT : sum;
+    *total = bestT;
     return SP_OK;
 }
 
@@ -1620,7 +1684,6 @@ sp_status sp_set_batching(sp_ctx* c, const int32_t* waves, const int32_t* persis
     for (int q = 0; q < kNumBuckets; ++q) {
         c->bk[q].waves = waves[q];
         c->bk[q].persist = persistent[q];
-        c->bk[q].bwaves = 0;   // blocked launches follow the new W
     }
     if (c->have_floes) SP_TRY(prepare_buckets(c));
     return SP_OK;
