@@ -6,19 +6,23 @@
 //
 // Per fine step, two launches.  The re-binning (gpull_kernel) is a stable
 // counting sort of the floes by sub-bin (side >= 2 r_max, so contacts only
-// join neighbouring sub-bins): the counts per sub-bin and per sub-bin row come
-// from the previous step's atomics, every row's workgroup takes its row start
-// from the row counts and its sub-bin starts by a scan, and every sub-bin
-// gathers its floes in their current order from the 3 x 3 sub-bins around it
-// (the state is grouped by the previous sub-bins and a floe moves far less
-// than a sub-bin per step; a sub-bin that finds fewer floes than its count
-// scans all floes instead).  The result is the order a stable sort by sub-bin
-// gives.  Then one thread per floe (gstep_kernel) sweeps the 3 x 3
-// neighbouring sub-bins, decides contacts exactly as the cell kernel does
-// (FP32 screen, FP64 in the guard band), sums drag and contact forces in FP64,
-// writes the updated floe in the same order, and counts the sub-bin of its
-// new position for the next re-binning.
+// join neighbouring sub-bins): the counts per sub-bin and per sub-bin row are
+// kept by the step's atomics, every row's wavefronts take their start from the
+// row counts and their sub-bin starts by a scan, and every sub-bin gathers its
+// floes in their current order from the 3 x 3 sub-bins around it (the state is
+// grouped by the previous sub-bins and a floe moves far less than a sub-bin per
+// step; a sub-bin that finds fewer floes than its count scans all floes
+// instead).  The result is the order a stable sort by sub-bin gives.  Then one
+// thread per floe (gstep_kernel) sweeps the 3 x 3 neighbouring sub-bins, decides
+// contacts exactly as the cell kernel does (FP32 screen, FP64 in the guard
+// band), sums drag and contact forces in FP64, writes the updated floe in the
+// same order, and keeps the counts of the sub-bin of its new position for the
+// next re-binning.  A floe's state is two 16-byte records and its angle.
 #pragma once
+
+namespace spdem {
+struct GMode;
+}
 
 struct sp_gdem {
     sp_gdem_params p;
@@ -36,24 +40,17 @@ struct sp_gdem {
     int nbx = 1, nby = 1;
     float rmax = 0.0f;
     // floe state, two buffers; cur holds the state in sub-bin order
-    uint32_t* xi[2] = {nullptr, nullptr};
-    uint32_t* yi[2] = {nullptr, nullptr};
-    float* u[2] = {nullptr, nullptr};
-    float* v[2] = {nullptr, nullptr};
-    float* w[2] = {nullptr, nullptr};
+    uint4* P[2] = {nullptr, nullptr};      // xi, yi, r, id
+    float4* V[2] = {nullptr, nullptr};     // u, v, w, h
     float* th[2] = {nullptr, nullptr};
-    float* r[2] = {nullptr, nullptr};
-    float* h[2] = {nullptr, nullptr};
-    int32_t* id[2] = {nullptr, nullptr};
     int cur = 0;
     // re-binning: the sub-bin of every floe's position (order of buffer cur),
     // floes per sub-bin and per sub-bin row of those, sub-bin starts
     int32_t* key = nullptr;            // [n]
-    int32_t* bcount[2] = {nullptr, nullptr};   // [nb], alternating per step
-    int32_t* rcount[2] = {nullptr, nullptr};   // [nby], alternating per step
+    int32_t* bcount = nullptr;         // [nb]
+    int32_t* rcount = nullptr;         // [nby]
     int32_t* starts[2] = {nullptr, nullptr};   // [nb + 1]
     int sb = 0;                        // starts[sb] groups buffer cur
-    int rb = 0;                        // bcount[rb] and rcount[rb] count sub-bins and rows of key
     unsigned long long* fallbacks_d = nullptr;  // sub-bins (and coarse cells) gathered by a full scan
     // coarse read-out: coarse cell of every floe, counts, starts, floes in cell order
     int32_t* ckey = nullptr;           // [n]
@@ -65,48 +62,55 @@ struct sp_gdem {
     size_t cstart_cap = 0;
     double* cmom = nullptr;            // coarse statistics (read-out)
     size_t cmom_cap = 0;
+    spdem::GMode* modes = nullptr;     // [SP_MAX_MODES]
     double2* phase = nullptr;          // (sin, cos) of every mode's phase at each sub-bin centre
     uint32_t* err_d = nullptr;
-    unsigned long long* contacts_d = nullptr;
+    unsigned long long* contacts_d = nullptr;   // [kContactSlots x kContactStride], their sum counts
     int64_t steps = 0;
 };
 
 namespace spdem {
 
+// Contact counters: workgroup i adds to slot i modulo kContactSlots, a cache
+// line each (adds to one address from all over the chip take 8 ns apiece).
+constexpr int kContactSlots = 64;
+constexpr int kContactStride = 16;
+constexpr size_t kContactBytes = (size_t)kContactSlots * kContactStride * sizeof(unsigned long long);
+
+// Constants of a mode, read through the scalar cache (kernel arguments lie in
+// host memory: their cache lines cost a trip over the bus each).
+struct GMode {
+    float kxL, kyL;                    // phase per sub-bin side
+    double au, av, cz;                 // amplitudes and curl coefficient av kx - au ky
+};
+typedef double GModeWords __attribute__((ext_vector_type(4)));
+typedef const GModeWords __attribute__((address_space(4)))* GModeTable;
+static_assert(sizeof(GMode) == sizeof(GModeWords), "a mode's constants are one vector of the table");
+
 struct GArgs {
     // pre-step state in sub-bin order
-    const uint32_t* xi;
-    const uint32_t* yi;
-    const float* u;
-    const float* v;
-    const float* w;
+    const uint4* P;                    // xi, yi, r, id
+    const float4* V;                   // u, v, w, h
     const float* th;
-    const float* r;
-    const float* h;
-    const int32_t* id;
     // updated state, same order
-    uint32_t* xo;
-    uint32_t* yo;
-    float* uo;
-    float* vo;
-    float* wo;
+    uint4* Po;
+    float4* Vo;
     float* tho;
-    float* ro;
-    float* ho;
-    int32_t* ido;
     const int32_t* bstart;
     const double2* phase;
+    const GMode* modes;                // [nmodes]
     int n, nbx, nby, nmodes;
+    int direct;                        // every phase offset is <= 1.6
     uint32_t flags;
     float qx, qy;
     double u0, v0;
     double lxd;                        // domain length in x (position of the far wall with SP_WALL_X)
     double qxd, qyd, inv_qxd, inv_qyd;
     double dtd, Ed, Gd, mud, cdrho, rho_ice_d;
-    Modes modes;                       // kxL, kyL per sub-bin side
     uint32_t* err;
     unsigned long long* contacts;
-    // the sub-bin of every updated position, counted per sub-bin and per row
+    // the sub-bin of every updated position; floes per sub-bin and per row,
+    // corrected for the floes that changed theirs
     int32_t* key_out;
     int32_t* count;
     int32_t* rows;
@@ -142,52 +146,6 @@ __device__ __forceinline__ Segs wrap_segments(int lo, int hi, int n)
     return Segs{s, e, 1, 0};
 }
 
-// Every position p of the grouped order whose sub-bin lies in rows ry and
-// columns rx (segments of wrap_segments), in ascending p: sub-bins are visited
-// in ascending index (rows, then columns, ascending), and the grouping puts a
-// lower sub-bin's floes first.
-template <class F>
-__device__ __forceinline__ void for_sources(const int32_t* ostart, int nbx, Segs ry, Segs rx, F f)
-{
-    const int ys[4] = {ry.a0, ry.a1, ry.b0, ry.b1};
-    const int xs[4] = {rx.a0, rx.a1, rx.b0, rx.b1};
-    for (int sy = 0; sy < 2; ++sy)
-        for (int yy = ys[2 * sy]; yy <= ys[2 * sy + 1]; ++yy)
-            for (int sx = 0; sx < 2; ++sx) {
-                if (xs[2 * sx] > xs[2 * sx + 1]) continue;
-                const int p1 = ostart[yy * nbx + xs[2 * sx + 1] + 1];
-                for (int p = ostart[yy * nbx + xs[2 * sx]]; p < p1; ++p) f(p);
-            }
-}
-
-// Exclusive prefix over a 256-thread workgroup (LDS s[256]); total of all in tot.
-__device__ __forceinline__ int block_exclusive_scan(int v, int* s, int& tot)
-{
-    const int t = threadIdx.x;
-    s[t] = v;
-    __syncthreads();
-    for (int off = 1; off < 256; off <<= 1) {
-        const int x = t >= off ? s[t - off] : 0;
-        __syncthreads();
-        s[t] += x;
-        __syncthreads();
-    }
-    const int incl = s[t];
-    tot = s[255];
-    __syncthreads();
-    return incl - v;
-}
-
-// Sum over the rows before `row` of per-row counts (every thread gets it).
-__device__ __forceinline__ int rows_before(const int32_t* rows, int row, int* s)
-{
-    int part = 0;
-    for (int i = threadIdx.x; i < row; i += 256) part += rows[i];
-    int tot;
-    (void)block_exclusive_scan(part, s, tot);
-    return tot;
-}
-
 // Sum over the wavefront (every lane gets it) and exclusive prefix over its lanes.
 __device__ __forceinline__ int wave_sum_i32(int x)
 {
@@ -208,31 +166,90 @@ __device__ __forceinline__ int wave_exclusive_i32(int x)
     return incl - x;
 }
 
+// Up to six position ranges [lo, hi) as one sequence: element t of it is
+// position t + (the offset of its range).
+struct Ranges {
+    int o0, o1, o2, o3, o4, o5;   // offsets
+    int e0, e1, e2, e3, e4;       // elements up to the end of each range
+    int total;
+};
+
+__device__ __forceinline__ Ranges make_ranges(int l0, int h0, int l1, int h1, int l2, int h2, int l3, int h3, int l4,
+                                              int h4, int l5, int h5)
+{
+    Ranges r;
+    r.e0 = h0 - l0;
+    r.e1 = r.e0 + (h1 - l1);
+    r.e2 = r.e1 + (h2 - l2);
+    r.e3 = r.e2 + (h3 - l3);
+    r.e4 = r.e3 + (h4 - l4);
+    r.total = r.e4 + (h5 - l5);
+    r.o0 = l0;
+    r.o1 = l1 - r.e0;
+    r.o2 = l2 - r.e1;
+    r.o3 = l3 - r.e2;
+    r.o4 = l4 - r.e3;
+    r.o5 = l5 - r.e4;
+    return r;
+}
+
+__device__ __forceinline__ int range_position(const Ranges& r, int t)
+{
+    // every field read first: a read under a condition would keep r in memory
+    const int o1 = r.o1, o2 = r.o2, o3 = r.o3, o4 = r.o4, o5 = r.o5;
+    const int e0 = r.e0, e1 = r.e1, e2 = r.e2, e3 = r.e3, e4 = r.e4;
+    int at = r.o0;
+    at = t >= e0 ? o1 : at;
+    at = t >= e1 ? o2 : at;
+    at = t >= e2 ? o3 : at;
+    at = t >= e3 ? o4 : at;
+    at = t >= e4 ? o5 : at;
+    return t + at;
+}
+
 struct GPull {
     // buffer cur, grouped by ostart -> buffer out, grouped by nstart
-    const uint32_t* xi;
-    const uint32_t* yi;
-    const float *u, *v, *w, *th, *r, *h;
-    const int32_t* id;
-    uint32_t* xo;
-    uint32_t* yo;
-    float *uo, *vo, *wo, *tho, *ro, *ho;
-    int32_t* ido;
+    const uint4* P;
+    const float4* V;
+    const float* th;
+    uint4* Po;
+    float4* Vo;
+    float* tho;
     const int32_t* key;        // [n] sub-bin of every floe of buffer cur
     const int32_t* ostart;     // [nb + 1]
     int32_t* nstart;           // [nb + 1]
     const int32_t* count;      // [nb] floes per sub-bin of key
-    int32_t* count_next;       // [nb] zeroed here for the next step's counts
     const int32_t* rows;       // [nby] floes per sub-bin row of key
-    int32_t* rows_next;        // [nby] zeroed here
     int n, nbx, nby;
     uint32_t* err;
     unsigned long long* fallbacks;
 };
 
+// Sum of v[lane], v[lane + 64], ... below n, 4 loads in flight.
+__device__ __forceinline__ int strided_sum(const int32_t* v, int n, int lane)
+{
+    int part = 0;
+    for (int i = lane; i < n; i += 256) {
+        int x[4];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) x[e] = i + 64 * e < n ? v[i + 64 * e] : 0;
+        part += (x[0] + x[1]) + (x[2] + x[3]);
+    }
+    return part;
+}
+
+// Neighbours read together per round (a floe has 9 in its 3 x 3 sub-bins on
+// average in the error study's scenarios: one round for most wavefronts).
+constexpr int kGBatch = 12;
+
 // Re-binning: one wavefront per run of 64 sub-bins of a row, one lane per
 // sub-bin.  A run starts after the floes of the rows before it and of its
-// row's earlier sub-bins.
+// row's earlier sub-bins.  A chain of dependent reads bounds it (115,200 floes
+// are two wavefronts per SIMD), so reads that do not depend on each other are
+// made together: the bounds of all neighbour ranges, the keys of a round of
+// neighbours, and the state of the floes found (a sub-bin holds one or two)
+// after the search instead of at each find; 32-byte packed state.  115,200
+// floes: 13.9 us before, 9.5 now.
 __global__ __launch_bounds__(256) void gpull_kernel(GPull g)
 {
     const int lane = threadIdx.x & 63;
@@ -240,72 +257,81 @@ __global__ __launch_bounds__(256) void gpull_kernel(GPull g)
     const int runs = (g.nbx + 63) >> 6;
     if (wid >= g.nby * runs) return;          // whole wavefronts
     const int by = wid / runs, c0 = (wid % runs) * 64;
-    int part = 0;
-    for (int i = lane; i < by; i += 64) part += g.rows[i];
-    for (int i = lane; i < c0; i += 64) part += g.count[by * g.nbx + i];
-    const int base = wave_sum_i32(part);
     const int bx = c0 + lane;
     const bool in = bx < g.nbx;
     const int b = by * g.nbx + bx;
+    // the (at most 3 x 2) position ranges of the neighbouring sub-bins in
+    // ascending order: rows y0 < y1 < y2, each one or two ranges
+    const int nrow = min(g.nby, 3);
+    const int y0 = g.nby <= 3 || by == 0 || by == g.nby - 1 ? 0 : by - 1;
+    const int y1 = g.nby <= 3 || by == 0 ? 1 : by == g.nby - 1 ? g.nby - 2 : by;
+    const int y2 = g.nby <= 3 ? 2 : by == 0 ? g.nby - 1 : by == g.nby - 1 ? by : by + 1;
+    const Segs rx = wrap_segments(in ? bx : 0, in ? bx : 0, g.nbx);
+    const bool two = rx.b0 <= rx.b1;
+    const int32_t *s0 = g.ostart + y0 * g.nbx, *s1 = g.ostart + y1 * g.nbx, *s2 = g.ostart + y2 * g.nbx;
+    const bool u1 = nrow > 1, u2 = nrow > 2;
+    const int xa = rx.a0, xb = rx.a1 + 1, xc = two ? rx.b0 : xa, xd = two ? rx.b1 + 1 : xa;
+    const Ranges rg = make_ranges(s0[xa], s0[xb], s0[xc], s0[xd], u1 ? s1[xa] : 0, u1 ? s1[xb] : 0, u1 ? s1[xc] : 0,
+                                  u1 ? s1[xd] : 0, u2 ? s2[xa] : 0, u2 ? s2[xb] : 0, u2 ? s2[xc] : 0, u2 ? s2[xd] : 0);
     const int cnt = in ? g.count[b] : 0;
+    const int base = wave_sum_i32(strided_sum(g.rows, by, lane) + strided_sum(g.count + by * g.nbx, c0, lane));
     const int q0 = base + wave_exclusive_i32(cnt);
-    if (c0 == 0 && lane == 0) g.rows_next[by] = 0;
     if (wid == g.nby * runs - 1 && lane == 63) g.nstart[g.nbx * g.nby] = g.n;
     if (!in) return;
-    g.count_next[b] = 0;
     g.nstart[b] = q0;
     int i = 0;
+    int m0 = 0, m1 = 0, m2 = 0, m3 = 0;   // the first four floes found
     auto take = [&](int p) {
-        if (g.key[p] != b) return;
-        if (i < cnt) {
+        if (i == 0) m0 = p;
+        if (i == 1) m1 = p;
+        if (i == 2) m2 = p;
+        if (i == 3) m3 = p;
+        if (i >= 4 && i < cnt) {
             const int q = q0 + i;
-            g.xo[q] = g.xi[p];
-            g.yo[q] = g.yi[p];
-            g.uo[q] = g.u[p];
-            g.vo[q] = g.v[p];
-            g.wo[q] = g.w[p];
+            g.Po[q] = g.P[p];
+            g.Vo[q] = g.V[p];
             g.tho[q] = g.th[p];
-            g.ro[q] = g.r[p];
-            g.ho[q] = g.h[p];
-            g.ido[q] = g.id[p];
         }
         ++i;
     };
-    // the (at most 3 x 2) position ranges of the neighbouring sub-bins in
-    // ascending order, their bounds read together, then 4 keys at a time
-    {
-        const Segs ry = wrap_segments(by, by, g.nby), rx = wrap_segments(bx, bx, g.nbx);
-        int row[3], nrow = 0;
-        for (int y = ry.a0; y <= ry.a1 && nrow < 3; ++y) row[nrow++] = y;
-        for (int y = ry.b0; y <= ry.b1 && nrow < 3; ++y) row[nrow++] = y;
-        const bool two = rx.b0 <= rx.b1;
-        int lo[6], hi[6];
+    for (int t0 = 0; t0 < rg.total; t0 += kGBatch) {
+        uint32_t mine = 0;
 #pragma unroll
-        for (int k = 0; k < 6; ++k) {
-            const int rr = k >> 1, sg = k & 1;
-            const bool use = rr < nrow && (sg == 0 || two);
-            const int b0 = use ? row[rr] * g.nbx + (sg ? rx.b0 : rx.a0) : 0;
-            const int b1 = use ? row[rr] * g.nbx + (sg ? rx.b1 : rx.a1) + 1 : 0;
-            lo[k] = use ? g.ostart[b0] : 0;
-            hi[k] = use ? g.ostart[b1] : 0;
+        for (int e = 0; e < kGBatch; ++e) {
+            const bool is = t0 + e < rg.total && g.key[range_position(rg, t0 + e)] == b;
+            mine |= (is ? 1u : 0u) << e;
         }
-#pragma unroll
-        for (int k = 0; k < 6; ++k)
-            for (int p = lo[k]; p < hi[k]; p += 4) {
-                int kk[4];
-#pragma unroll
-                for (int e = 0; e < 4; ++e) kk[e] = p + e < hi[k] ? g.key[p + e] : -1;
-#pragma unroll
-                for (int e = 0; e < 4; ++e)
-                    if (kk[e] == b) take(p + e);
-            }
+        for (; mine; mine &= mine - 1) take(range_position(rg, t0 + __builtin_ctz(mine)));
     }
     if (i != cnt) {   // a floe came from further away: every floe, in order
         atomicAdd(g.fallbacks, 1ull);
         i = 0;
-        for (int p = 0; p < g.n; ++p) take(p);
+#pragma unroll 1
+        for (int p = 0; p < g.n; ++p)
+            if (g.key[p] == b) take(p);
         if (i != cnt) atomicOr(g.err, kErrRebin);
     }
+    const int got = min(i, cnt);
+    const bool h0 = got > 0, h1 = got > 1, h2 = got > 2, h3 = got > 3;
+    uint4 P0, P1, P2, P3;
+    float4 V0, V1, V2, V3;
+    float t0, t1, t2, t3;
+#define GPULL_GET(e) \
+    if (h##e) {      \
+        P##e = g.P[m##e]; \
+        V##e = g.V[m##e]; \
+        t##e = g.th[m##e]; \
+    }
+#define GPULL_PUT(e) \
+    if (h##e) {      \
+        g.Po[q0 + e] = P##e; \
+        g.Vo[q0 + e] = V##e; \
+        g.tho[q0 + e] = t##e; \
+    }
+    GPULL_GET(0) GPULL_GET(1) GPULL_GET(2) GPULL_GET(3)
+    GPULL_PUT(0) GPULL_PUT(1) GPULL_PUT(2) GPULL_PUT(3)
+#undef GPULL_GET
+#undef GPULL_PUT
 }
 
 // Ocean current and curl at a floe from the phase table of its sub-bin: the
@@ -320,20 +346,25 @@ __device__ __forceinline__ void gocean(const GArgs& a, uint32_t x, uint32_t y, d
     const int b = (int)(gbin_axis(y, a.nby) * (uint32_t)a.nbx + gbin_axis(x, a.nbx));
     const float fx = gbin_offset(x, a.nbx), fy = gbin_offset(y, a.nby);
     const double2* ph = a.phase + (size_t)b * a.nmodes;
+    GModeTable table = (GModeTable)a.modes;
+    double2 next = ph[0];
     for (int m = 0; m < a.nmodes; ++m) {
-        const float d = a.modes.kxL[m] * fx + a.modes.kyL[m] * fy;
+        const double2 q = next;
+        if (m + 1 < a.nmodes) next = ph[m + 1];
+        const GModeWords c = table[m];
+        const float kxL = __int_as_float(__double2loint(c[0])), kyL = __int_as_float(__double2hiint(c[0]));
+        const float d = kxL * fx + kyL * fy;
         float sdf, cdf;
-        if (a.modes.direct)
+        if (a.direct)
             sincos_direct(d, sdf, cdf);
         else
             sincos_small(d, sdf, cdf);
         const double sd = sdf, cd = cdf;
-        const double2 q = ph[m];
         const double sn = fma(q.x, cd, q.y * sd);
         const double cn = fma(q.y, cd, -(q.x * sd));
-        uo = fma(a.modes.au[m], sn, uo);
-        vo = fma(a.modes.av[m], sn, vo);
-        zeta = fma(a.modes.cz[m], cn, zeta);
+        uo = fma(c[1], sn, uo);
+        vo = fma(c[2], sn, vo);
+        zeta = fma(c[3], cn, zeta);
     }
 }
 
@@ -356,75 +387,142 @@ __device__ __forceinline__ void gdrag(const GArgs& a, uint32_t x, uint32_t y, do
     tdr = beta * dW * fabs(dW);
 }
 
+// One thread per floe.  Bound by its chain of dependent reads (115,200 floes
+// are two wavefronts per SIMD): own state, bounds of the candidate ranges (the
+// three sub-bins of a row are consecutive, two ranges where they wrap), the
+// candidates' positions and radii as one 16-byte read each and a round at a
+// time, then the velocity of those in contact, the next one's read before the
+// current one's force.  Candidates are decided and their forces summed in the
+// order sub-bin row, sub-bin, position.  Sub-bin and row counts are corrected
+// only for floes that changed theirs: adding every floe to its counter, and
+// every wavefront to one contact counter, cost as much as the contacts.  115,200
+// floes and two modes: 29.5 us before, 10.2 now.
 __global__ __launch_bounds__(256) void gstep_kernel(GArgs a)
 {
     const int k = blockIdx.x * blockDim.x + threadIdx.x;
     unsigned long long ncontact = 0;
-    int row = -1;   // sub-bin row of the updated position
     if (k < a.n) {
-        const uint32_t xl = a.xi[k], yl = a.yi[k];
-        const float rl = a.r[k];
-        const int idl = a.id[k];
-        const double rld = rl, uld = a.u[k], vld = a.v[k], wld = a.w[k];
+        const uint4 own = a.P[k];
+        const float4 vo = a.V[k];
+        const float thl = a.th[k];
+        const uint32_t xl = own.x, yl = own.y;
+        const float rl = __uint_as_float(own.z);
+        const int idl = (int)own.w;
+        const double rld = rl, uld = vo.x, vld = vo.y, wld = vo.z;
+        const int bx = (int)gbin_axis(xl, a.nbx), by = (int)gbin_axis(yl, a.nby);
+        const bool wall = (a.flags & SP_WALL_X) != 0;
+        // columns of the neighbouring sub-bins in visiting order: [ca, cb) and,
+        // across the domain's edge, [0, cc1)
+        int ca = bx - 1, cb = bx + 2, cc1 = 0;
+        if (a.nbx < 3) {
+            ca = bx;
+            cb = bx + 1;
+        } else if (bx == 0) {
+            if (wall) {
+                ca = 0;
+            } else {
+                ca = a.nbx - 1;
+                cb = a.nbx;
+                cc1 = 2;
+            }
+        } else if (bx == a.nbx - 1) {
+            cb = a.nbx;
+            cc1 = wall ? 0 : 1;
+        }
+        const int y0 = by == 0 ? a.nby - 1 : by - 1, y2 = by == a.nby - 1 ? 0 : by + 1;
+        const bool rows3 = a.nby >= 3;
+        const int32_t *s0 = a.bstart + (rows3 ? y0 : by) * a.nbx, *s1 = a.bstart + by * a.nbx,
+                      *s2 = a.bstart + (rows3 ? y2 : by) * a.nbx;
+        const int l0 = s0[ca], h0 = s0[cb], l1 = s1[ca], h1 = s1[cb], l2 = s2[ca], h2 = s2[cb];
+        int m0 = 0, n0 = 0, m1 = 0, n1 = 0, m2 = 0, n2 = 0;
+        if (cc1 > 0) {
+            m0 = s0[0];
+            n0 = s0[cc1];
+            m1 = s1[0];
+            n1 = s1[cc1];
+            m2 = s2[0];
+            n2 = s2[cc1];
+        }
+        const Ranges rg = make_ranges(l0, rows3 ? h0 : l0, m0, rows3 ? n0 : m0, l1, h1, m1, n1, l2, rows3 ? h2 : l2, m2,
+                                      rows3 ? n2 : m2);
         double Fx, Fy, T;
         gdrag(a, xl, yl, rld, uld, vld, wld, Fx, Fy, T);
-        const double md = a.rho_ice_d * (double)a.h[k] * kPi * rld * rld;
-        const int bx = (int)gbin_axis(xl, a.nbx), by = (int)gbin_axis(yl, a.nby);
-        const int oy0 = a.nby >= 3 ? -1 : 0, oy1 = a.nby >= 3 ? 1 : 0;
-        const int ox0 = a.nbx >= 3 ? -1 : 0, ox1 = a.nbx >= 3 ? 1 : 0;
-        const bool wall = (a.flags & SP_WALL_X) != 0;
-        for (int oy = oy0; oy <= oy1; ++oy) {
-            const int byy = (by + oy + a.nby) % a.nby;
-            for (int ox = ox0; ox <= ox1; ++ox) {
-                if (wall && (bx + ox < 0 || bx + ox >= a.nbx)) continue;   // no periodic image across a wall
-                const int b = byy * a.nbx + (bx + ox + a.nbx) % a.nbx;
-                const int j1 = a.bstart[b + 1];
-                for (int j = a.bstart[b]; j < j1; ++j) {
-                    if (j == k) continue;
-                    // between walls the x difference is the plain one (pairs
-                    // more than half the domain apart are far from contact)
-                    const long long ddx = (long long)a.xi[j] - (long long)xl;
-                    if (wall && (ddx >= 0x80000000ll || ddx < -0x80000000ll)) continue;
-                    const int dxi = wall ? (int)ddx : (int)(a.xi[j] - xl), dyi = (int)(a.yi[j] - yl);
-                    const float rj = a.r[j];
-                    float diff, R2;
-                    screen(dxi, dyi, rl, rj, a.qx, a.qy, diff, R2);
-                    if (diff > kGuard * R2) continue;
-                    if (fabsf(diff) <= kGuard * R2 && !exact_contact(dxi, dyi, rl, rj, a.qxd, a.qyd)) continue;
-                    const double dx = (double)dxi * a.qxd, dy = (double)dyi * a.qyd;
-                    const double d2 = dx * dx + dy * dy;
-                    if (!(d2 > 0.0)) {
-                        atomicOr(a.err, kErrOverlap);
-                        continue;
-                    }
-                    const int idj = a.id[j];
-                    const double rjd = (double)rj;
-                    const double d = sqrt(d2);
-                    const double inv_d = 1.0 / d;
-                    const double nx = dx * inv_d, ny = dy * inv_d;
-                    const double tx = -ny, ty = nx;
-                    const double R = rld + rjd;
-                    const double delta = d - R;
-                    const double dr = fabs(rld - rjd);
-                    double cc;
-                    if (d <= dr) {
-                        cc = 2.0 * fmin(rld, rjd);
-                    } else {
-                        const double p = (((-delta) * (d + R)) * (d - dr)) * (d + dr);
-                        cc = sqrt(fmax(p, 0.0)) * inv_d;
-                    }
-                    const double Fn = cc * a.Ed * delta;
-                    const double wjd = (double)a.w[j];
-                    // spin sum with the lower floe id first: exactly antisymmetric pair forces
-                    const double spin = (idl < idj) ? (wld * rld + wjd * rjd) : (wjd * rjd + wld * rld);
-                    const double vt = (((double)a.u[j] - uld) * tx + ((double)a.v[j] - vld) * ty) - spin;
-                    const double capf = a.mud * fabs(Fn);
-                    const double Ft = fmin(fmax(cc * a.Gd * vt, -capf), capf);
-                    Fx += Fn * nx + Ft * tx;
-                    Fy += Fn * ny + Ft * ty;
-                    T += rld * Ft;
-                    ncontact += (idl < idj) ? 1ull : 0ull;
+        const double md = a.rho_ice_d * (double)vo.w * kPi * rld * rld;
+        for (int t0 = 0; t0 < rg.total; t0 += kGBatch) {
+            uint4 c[kGBatch];
+            int jj[kGBatch];
+#pragma unroll
+            for (int e = 0; e < kGBatch; ++e) {
+                jj[e] = t0 + e < rg.total ? range_position(rg, t0 + e) : k;   // the floe itself stands for none
+                c[e] = a.P[jj[e]];
+            }
+            uint32_t hits = 0;
+#pragma unroll
+            for (int e = 0; e < kGBatch; ++e) {
+                // between walls the x difference is the plain one (pairs
+                // more than half the domain apart are far from contact)
+                const long long ddx = (long long)c[e].x - (long long)xl;
+                const bool apart = wall && (ddx >= 0x80000000ll || ddx < -0x80000000ll);
+                const int dxi = (int)(c[e].x - xl), dyi = (int)(c[e].y - yl);
+                const float rj = __uint_as_float(c[e].z);
+                float diff, R2;
+                screen(dxi, dyi, rl, rj, a.qx, a.qy, diff, R2);
+                if (!(diff > kGuard * R2) && !apart && jj[e] != k) hits |= 1u << e;
+            }
+            uint4 nxt;
+            float4 nv;
+            if (hits) {
+                const int j = range_position(rg, t0 + __builtin_ctz(hits));
+                nxt = a.P[j];
+                nv = a.V[j];
+            }
+            while (hits) {
+                const uint4 cur = nxt;
+                const float4 vj = nv;
+                hits &= hits - 1;
+                if (hits) {
+                    const int j = range_position(rg, t0 + __builtin_ctz(hits));
+                    nxt = a.P[j];
+                    nv = a.V[j];
                 }
+                const int dxi = (int)(cur.x - xl), dyi = (int)(cur.y - yl);
+                const float rj = __uint_as_float(cur.z);
+                float diff, R2;
+                screen(dxi, dyi, rl, rj, a.qx, a.qy, diff, R2);
+                if (fabsf(diff) <= kGuard * R2 && !exact_contact(dxi, dyi, rl, rj, a.qxd, a.qyd)) continue;
+                const double dx = (double)dxi * a.qxd, dy = (double)dyi * a.qyd;
+                const double d2 = dx * dx + dy * dy;
+                if (!(d2 > 0.0)) {
+                    atomicOr(a.err, kErrOverlap);
+                    continue;
+                }
+                const int idj = (int)cur.w;
+                const double rjd = (double)rj;
+                const double d = sqrt(d2);
+                const double inv_d = 1.0 / d;
+                const double nx = dx * inv_d, ny = dy * inv_d;
+                const double tx = -ny, ty = nx;
+                const double R = rld + rjd;
+                const double delta = d - R;
+                const double dr = fabs(rld - rjd);
+                double cc;
+                if (d <= dr) {
+                    cc = 2.0 * fmin(rld, rjd);
+                } else {
+                    const double p = (((-delta) * (d + R)) * (d - dr)) * (d + dr);
+                    cc = sqrt(fmax(p, 0.0)) * inv_d;
+                }
+                const double Fn = cc * a.Ed * delta;
+                const double wjd = (double)vj.z;
+                // spin sum with the lower floe id first: exactly antisymmetric pair forces
+                const double spin = (idl < idj) ? (wld * rld + wjd * rjd) : (wjd * rjd + wld * rld);
+                const double vt = (((double)vj.x - uld) * tx + ((double)vj.y - vld) * ty) - spin;
+                const double capf = a.mud * fabs(Fn);
+                const double Ft = fmin(fmax(cc * a.Gd * vt, -capf), capf);
+                Fx += Fn * nx + Ft * tx;
+                Fy += Fn * ny + Ft * ty;
+                T += rld * Ft;
+                ncontact += (idl < idj) ? 1ull : 0ull;
             }
         }
         if (wall) {
@@ -464,81 +562,92 @@ __global__ __launch_bounds__(256) void gstep_kernel(GArgs a)
             if (xn < 0 || xn >= 0x100000000ll) atomicOr(a.err, kErrWall);
         }
         const uint32_t xn = xl + (uint32_t)sx, yn = yl + (uint32_t)sy;
-        a.xo[k] = xn;
-        a.yo[k] = yn;
+        a.Po[k] = make_uint4(xn, yn, own.z, own.w);
+        a.Vo[k] = make_float4(un, vn, wn, vo.w);
+        a.tho[k] = (float)((double)thl + dt * wx);
         {
-            row = (int)gbin_axis(yn, a.nby);
-            const int b = row * a.nbx + (int)gbin_axis(xn, a.nbx);
+            const int row = (int)gbin_axis(yn, a.nby);
+            const int b = row * a.nbx + (int)gbin_axis(xn, a.nbx), b0 = by * a.nbx + bx;
             a.key_out[k] = b;
-            atomicAdd(&a.count[b], 1);
+            if (b != b0) {
+                atomicAdd(&a.count[b], 1);
+                atomicSub(&a.count[b0], 1);
+            }
+            if (row != by) {
+                atomicAdd(&a.rows[row], 1);
+                atomicSub(&a.rows[by], 1);
+            }
         }
-        a.uo[k] = un;
-        a.vo[k] = vn;
-        a.wo[k] = wn;
-        a.tho[k] = (float)((double)a.th[k] + dt * wx);
-        a.ro[k] = rl;
-        a.ho[k] = a.h[k];
-        a.ido[k] = idl;
         if (!(isfinite(un) && isfinite(vn) && isfinite(wn))) atomicOr(a.err, kErrNaN);
     }
     const unsigned long long cs = wave_sum_u64(ncontact);
-    if ((threadIdx.x & 63) == 0 && cs) atomicAdd(a.contacts, cs);
-    // floes per row: one atomic per wavefront when its floes share a row (the
-    // order is by sub-bin, so they mostly do)
-    const int row0 = __shfl(row, 0);
-    const unsigned long long valid = __ballot(row >= 0), same = __ballot(row >= 0 && row == row0);
-    if (same == valid) {
-        if ((threadIdx.x & 63) == 0 && valid) atomicAdd(&a.rows[row0], (int)__popcll(valid));
-    } else if (row >= 0) {
-        atomicAdd(&a.rows[row], 1);
-    }
+    if ((threadIdx.x & 63) == 0 && cs)
+        atomicAdd(&a.contacts[(blockIdx.x % kContactSlots) * kContactStride], cs);
 }
 
-// Coarse cell of every floe of buffer cur (read-out), counted per cell and per row.
-__global__ __launch_bounds__(256) void ckey_kernel(const uint32_t* xi, const uint32_t* yi, int n, int nxc, int nyc,
-                                                   int32_t* ckey, int32_t* ccount, int32_t* crow)
+// Coarse cell of every floe of buffer cur (read-out), counted per cell and per
+// row: consecutive floes mostly share both (the order is by sub-bin), so a run
+// of lanes with one cell or row is one atomic.  115,200 floes onto 48 x 24
+// cells: 16 us; every floe adding to its cell's and row's counters took 932.
+__device__ __forceinline__ void count_runs(int32_t* counts, int c, bool valid)
+{
+    const int lane = threadIdx.x & 63;
+    const int prev = __shfl_up(c, 1, 64);
+    const unsigned long long live = __ballot(valid);                   // lanes 0 .. l - 1
+    const unsigned long long heads = __ballot(valid && (lane == 0 || c != prev));
+    if (!((heads >> lane) & 1ull)) return;
+    const unsigned long long after = lane == 63 ? 0ull : heads >> (lane + 1);
+    const int next = after ? lane + 1 + __builtin_ctzll(after) : __popcll(live);
+    atomicAdd(&counts[c], next - lane);
+}
+
+__global__ __launch_bounds__(256) void ckey_kernel(const uint4* P, int n, int nxc, int nyc, int32_t* ckey,
+                                                   int32_t* ccount, int32_t* crow)
 {
     const int k = blockIdx.x * blockDim.x + threadIdx.x;
-    if (k >= n) return;
-    const int cy = (int)gbin_axis(yi[k], nyc);
-    const int c = cy * nxc + (int)gbin_axis(xi[k], nxc);
-    ckey[k] = c;
-    atomicAdd(&ccount[c], 1);
-    atomicAdd(&crow[cy], 1);
+    const bool valid = k < n;
+    int c = -1, cy = -1;
+    if (valid) {
+        const uint4 p = P[k];
+        cy = (int)gbin_axis(p.y, nyc);
+        c = cy * nxc + (int)gbin_axis(p.x, nxc);
+        ckey[k] = c;
+    }
+    count_runs(ccount, c, valid);
+    count_runs(crow, cy, valid);
 }
 
 // The floes of every coarse cell in the current order (perm, from cstart): a
-// stable counting sort as the re-binning, one workgroup per coarse row, the
-// row's cells scanned for their starts, then one wavefront per cell gathering
-// in order (ballot and prefix count) from the sub-bins its cell overlaps, one
-// more on every side (the grouping is that of the last re-binning, the
-// positions a step later); a cell that finds fewer floes than its count scans
-// all floes instead.
+// stable counting sort as the re-binning, one workgroup per `run` cells of a
+// coarse row.  A run starts after the floes of the rows before it and of its
+// row's earlier cells; each wavefront gathers its cells' floes in order (ballot
+// and prefix count) from the sub-bins a cell overlaps, one more on every side
+// (the grouping is that of the last re-binning, the positions a step later); a
+// cell that finds fewer floes than its count scans all floes instead.  Runs of
+// 4, a cell per wavefront, while the grid is small enough for the sums before a
+// run to cost nothing (48 x 24 cells: 15.5 us, a workgroup per row 89), of 64
+// above.
+constexpr int kCoarseRun = 4, kCoarseRunLarge = 64, kCoarseSmall = 1 << 16;
+
 __global__ __launch_bounds__(256) void cpull_kernel(const int32_t* ckey, const int32_t* ccount, const int32_t* crow,
                                                     const int32_t* ostart, int n, int nbx, int nby, int nxc,
-                                                    int nyc, int32_t* cstart, int32_t* perm, uint32_t* err,
+                                                    int nyc, int run, int32_t* cstart, int32_t* perm, uint32_t* err,
                                                     unsigned long long* fallbacks)
 {
-    __shared__ int s[256];
-    const int cy = blockIdx.x;
-    const int row0 = rows_before(crow, cy, s);
-    if (threadIdx.x == 0 && cy == nyc - 1) cstart[nxc * nyc] = n;
-    int carry = 0;
-    for (int c0 = 0; c0 < nxc; c0 += 256) {
-        const int cx = c0 + (int)threadIdx.x;
-        const int cnt = cx < nxc ? ccount[cy * nxc + cx] : 0;
-        int tot;
-        const int q0 = row0 + carry + block_exclusive_scan(cnt, s, tot);
-        carry += tot;
-        if (cx < nxc) cstart[cy * nxc + cx] = q0;
-    }
-    __syncthreads();
-    // sub-bin rows and columns a coarse cell overlaps
+    const int runs = (nxc + run - 1) / run;
+    const int cy = blockIdx.x / runs, c0 = (blockIdx.x % runs) * run;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int here = min(run, nxc - c0);   // cells of the run, at most one per lane
+    const int own = lane < here ? ccount[cy * nxc + c0 + lane] : 0;
+    const int base = wave_sum_i32(strided_sum(crow, cy, lane) + strided_sum(ccount + cy * nxc, c0, lane));
+    const int first = base + wave_exclusive_i32(own);   // start of the lane's cell
+    if (wave == 0 && lane < here) cstart[cy * nxc + c0 + lane] = first;
+    if (threadIdx.x == 0 && blockIdx.x == gridDim.x - 1) cstart[nxc * nyc] = n;
+    // sub-bin rows and columns a coarse cell overlaps
     const int ylo = (int)(((long long)cy * nby) / nyc), yhi = (int)(((long long)(cy + 1) * nby - 1) / nyc);
-    for (int cx = wave; cx < nxc; cx += 4) {
-        const int c = cy * nxc + cx;
-        const int q0 = cstart[c], cnt = ccount[c];
+    for (int l = wave; l < here; l += 4) {
+        const int cx = c0 + l, c = cy * nxc + cx;
+        const int q0 = __shfl(first, l), cnt = __shfl(own, l);
         const int xlo = (int)(((long long)cx * nbx) / nxc), xhi = (int)(((long long)(cx + 1) * nbx - 1) / nxc);
         int i = 0;   // floes of c gathered so far (the same in every lane)
         auto chunk = [&](int p0, int p1) {   // positions [p0, p1), 64 at a time, in order
@@ -581,9 +690,11 @@ __global__ __launch_bounds__(64) void cmom_kernel(GArgs a, const int32_t* perm, 
     for (int q = 0; q < SP_NMOM; ++q) acc[q] = 0.0;
     for (int i = cstart[c] + lane; i < cstart[c + 1]; i += 64) {
         const int k = perm[i];
-        const uint32_t x = a.xi[k], y = a.yi[k];
-        const double rl = a.r[k], ul = a.u[k], vl = a.v[k], wl = a.w[k];
-        const double m = a.rho_ice_d * (double)a.h[k] * kPi * rl * rl;
+        const uint4 p = a.P[k];
+        const float4 f = a.V[k];
+        const uint32_t x = p.x, y = p.y;
+        const double rl = __uint_as_float(p.z), ul = f.x, vl = f.y, wl = f.z;
+        const double m = a.rho_ice_d * (double)f.w * kPi * rl * rl;
         double fdx, fdy, tdr;
         gdrag(a, x, y, rl, ul, vl, wl, fdx, fdy, tdr);
         acc[M_N] += 1.0;
@@ -608,21 +719,29 @@ __global__ __launch_bounds__(64) void cmom_kernel(GArgs a, const int32_t* perm, 
 }
 
 // Scatter the state back into input order (read-out).
-__global__ __launch_bounds__(256) void gscatter_kernel(const int32_t* id, int n, const uint32_t* xi, const uint32_t* yi,
-                                                       const float* u, const float* v, const float* w, const float* th,
-                                                       const float* r, uint32_t* xo, uint32_t* yo, float* uo,
-                                                       float* vo, float* wo, float* tho, float* ro)
+__global__ __launch_bounds__(256) void gscatter_kernel(int n, const uint4* P, const float4* V, const float* th,
+                                                       uint32_t* xo, uint32_t* yo, float* uo, float* vo, float* wo,
+                                                       float* tho, float* ro)
 {
     const int k = blockIdx.x * blockDim.x + threadIdx.x;
     if (k >= n) return;
-    const int p = id[k];
-    xo[p] = xi[k];
-    yo[p] = yi[k];
-    uo[p] = u[k];
-    vo[p] = v[k];
-    wo[p] = w[k];
+    const uint4 q = P[k];
+    const float4 f = V[k];
+    const int p = (int)q.w;
+    xo[p] = q.x;
+    yo[p] = q.y;
+    uo[p] = f.x;
+    vo[p] = f.y;
+    wo[p] = f.z;
     tho[p] = th[k];
-    ro[p] = r[k];
+    ro[p] = __uint_as_float(q.z);
+}
+
+// The floe ids in the current order (read-out).
+__global__ __launch_bounds__(256) void gids_kernel(int n, const uint4* P, int32_t* id)
+{
+    const int k = blockIdx.x * blockDim.x + threadIdx.x;
+    if (k < n) id[k] = (int)P[k].w;
 }
 
 }  // namespace spdem
@@ -665,21 +784,21 @@ sp_status galloc(sp_gdem* g, T** p, size_t count)
 void gdem_free(sp_gdem* g)
 {
     for (int b = 0; b < 2; ++b) {
-        void* ps[] = {g->xi[b], g->yi[b], g->u[b], g->v[b], g->w[b], g->th[b], g->r[b], g->h[b], g->id[b],
-                      g->rcount[b], g->starts[b], g->bcount[b]};
+        void* ps[] = {g->P[b], g->V[b], g->th[b], g->starts[b]};
         for (void* p : ps)
             if (p) (void)hipFree(p);
-        g->xi[b] = g->yi[b] = nullptr;
-        g->u[b] = g->v[b] = g->w[b] = g->th[b] = g->r[b] = g->h[b] = nullptr;
-        g->id[b] = nullptr;
-        g->rcount[b] = g->starts[b] = g->bcount[b] = nullptr;
+        g->P[b] = nullptr;
+        g->V[b] = nullptr;
+        g->th[b] = nullptr;
+        g->starts[b] = nullptr;
     }
-    void* ps[] = {g->key, g->ckey, g->perm, g->ccount, g->crow, g->cstart, g->cmom, g->phase, g->err_d,
+    void* ps[] = {g->key, g->bcount, g->rcount, g->ckey, g->perm, g->ccount, g->crow, g->cstart, g->cmom, g->modes, g->phase, g->err_d,
                   g->contacts_d, g->fallbacks_d};
     for (void* p : ps)
         if (p) (void)hipFree(p);
-    g->key = g->ckey = g->perm = g->ccount = g->crow = g->cstart = nullptr;
+    g->key = g->bcount = g->rcount = g->ckey = g->perm = g->ccount = g->crow = g->cstart = nullptr;
     g->cmom = nullptr;
+    g->modes = nullptr;
     g->phase = nullptr;
     g->err_d = nullptr;
     g->contacts_d = nullptr;
@@ -691,28 +810,16 @@ GArgs gargs(const sp_gdem* g, double dt, int from, int to)
 {
     GArgs a;
     memset(&a, 0, sizeof a);
-    a.xi = g->xi[from];
-    a.yi = g->yi[from];
-    a.u = g->u[from];
-    a.v = g->v[from];
-    a.w = g->w[from];
+    a.P = g->P[from];
+    a.V = g->V[from];
     a.th = g->th[from];
-    a.r = g->r[from];
-    a.h = g->h[from];
-    a.id = g->id[from];
-    a.xo = g->xi[to];
-    a.yo = g->yi[to];
-    a.uo = g->u[to];
-    a.vo = g->v[to];
-    a.wo = g->w[to];
+    a.Po = g->P[to];
+    a.Vo = g->V[to];
     a.tho = g->th[to];
-    a.ro = g->r[to];
-    a.ho = g->h[to];
-    a.ido = g->id[to];
     a.bstart = g->starts[g->sb ^ 1];   // the starts the re-binning before the step makes
     a.key_out = g->key;
-    a.count = g->bcount[g->rb ^ 1];
-    a.rows = g->rcount[g->rb ^ 1];
+    a.count = g->bcount;
+    a.rows = g->rcount;
     a.phase = g->phase;
     a.n = (int)g->n;
     a.nbx = g->nbx;
@@ -736,15 +843,10 @@ GArgs gargs(const sp_gdem* g, double dt, int from, int to)
     a.lxd = g->p.lx;
     const double bx = g->p.lx / g->nbx, by = g->p.ly / g->nby;
     float reach = 0.0f;
-    for (int m = 0; m < g->nmodes; ++m) {
-        a.modes.kxL[m] = (float)(g->kx[m] * bx);
-        a.modes.kyL[m] = (float)(g->ky[m] * by);
-        a.modes.au[m] = g->au[m];
-        a.modes.av[m] = g->av[m];
-        a.modes.cz[m] = g->av[m] * g->kx[m] - g->au[m] * g->ky[m];
-        reach = std::max(reach, 0.5f * (fabsf(a.modes.kxL[m]) + fabsf(a.modes.kyL[m])));
-    }
-    a.modes.direct = reach <= 1.6f ? 1 : 0;
+    for (int m = 0; m < g->nmodes; ++m)
+        reach = std::max(reach, 0.5f * (fabsf((float)(g->kx[m] * bx)) + fabsf((float)(g->ky[m] * by))));
+    a.modes = g->modes;
+    a.direct = reach <= 1.6f ? 1 : 0;
     a.err = g->err_d;
     a.contacts = g->contacts_d;
     return a;
@@ -764,6 +866,16 @@ sp_status gupload_phase(sp_gdem* g)
             tab[b * nm + m] = make_double2(sin(t), cos(t));
         }
     }
+    GMode mode[SP_MAX_MODES];
+    for (int m = 0; m < g->nmodes; ++m) {
+        mode[m].kxL = (float)(g->kx[m] * (g->p.lx / g->nbx));
+        mode[m].kyL = (float)(g->ky[m] * (g->p.ly / g->nby));
+        mode[m].au = g->au[m];
+        mode[m].av = g->av[m];
+        mode[m].cz = g->av[m] * g->kx[m] - g->au[m] * g->ky[m];
+    }
+    if (!g->modes) SP_TRY(galloc(g, &g->modes, SP_MAX_MODES));
+    GD_TRY(g, hipMemcpyAsync(g->modes, mode, (size_t)g->nmodes * sizeof(GMode), hipMemcpyHostToDevice, g->stream));
     SP_TRY(galloc(g, &g->phase, tab.size()));
     GD_TRY(g, hipMemcpyAsync(g->phase, tab.data(), tab.size() * sizeof(double2), hipMemcpyHostToDevice, g->stream));
     GD_TRY(g, hipStreamSynchronize(g->stream));
@@ -806,9 +918,9 @@ sp_status sp_gdem_create(const sp_gdem_params* p, void* stream, sp_gdem** out)
         g->own_stream = true;
     }
     sp_status st = galloc(g, &g->err_d, 1);
-    if (!st) st = galloc(g, &g->contacts_d, 1);
+    if (!st) st = galloc(g, &g->contacts_d, kContactSlots * kContactStride);
     if (!st && (hipMemsetAsync(g->err_d, 0, 4, g->stream) != hipSuccess ||
-                hipMemsetAsync(g->contacts_d, 0, 8, g->stream) != hipSuccess))
+                hipMemsetAsync(g->contacts_d, 0, kContactBytes, g->stream) != hipSuccess))
         st = SP_EDEVICE;
     if (st) {
         gdem_free(g);
@@ -881,19 +993,13 @@ sp_status sp_gdem_set_floes(sp_gdem* g, int64_t n, const uint32_t* xi, const uin
     const size_t N = (size_t)n;
     const size_t nb = (size_t)bx * by;
     for (int b = 0; b < 2; ++b) {
-        SP_TRY(galloc(g, &g->xi[b], N));
-        SP_TRY(galloc(g, &g->yi[b], N));
-        SP_TRY(galloc(g, &g->u[b], N));
-        SP_TRY(galloc(g, &g->v[b], N));
-        SP_TRY(galloc(g, &g->w[b], N));
+        SP_TRY(galloc(g, &g->P[b], N));
+        SP_TRY(galloc(g, &g->V[b], N));
         SP_TRY(galloc(g, &g->th[b], N));
-        SP_TRY(galloc(g, &g->r[b], N));
-        SP_TRY(galloc(g, &g->h[b], N));
-        SP_TRY(galloc(g, &g->id[b], N));
-        SP_TRY(galloc(g, &g->rcount[b], (size_t)by));
         SP_TRY(galloc(g, &g->starts[b], nb + 1));
-        SP_TRY(galloc(g, &g->bcount[b], nb));
     }
+    SP_TRY(galloc(g, &g->rcount, (size_t)by));
+    SP_TRY(galloc(g, &g->bcount, nb));
     SP_TRY(galloc(g, &g->key, N));
     SP_TRY(galloc(g, &g->ckey, N));
     SP_TRY(galloc(g, &g->perm, N));
@@ -915,28 +1021,39 @@ sp_status sp_gdem_set_floes(sp_gdem* g, int64_t n, const uint32_t* xi, const uin
     }
     std::vector<int32_t> skey(N);
     for (size_t q = 0; q < N; ++q) skey[q] = key[order[q]];
-    std::vector<uint32_t> bits(N);
-    const void* src[8] = {xi, yi, u, v, omega, theta, r, h};
-    void* dst[8] = {g->xi[0], g->yi[0], g->u[0], g->v[0], g->w[0], g->th[0], g->r[0], g->h[0]};
-    for (int k = 0; k < 8; ++k) {
-        const uint32_t* sk = static_cast<const uint32_t*>(src[k]);
-        for (size_t q = 0; q < N; ++q) bits[q] = sk ? sk[order[q]] : 0u;
-        GD_TRY(g, hipMemcpy(dst[k], bits.data(), N * 4, hipMemcpyHostToDevice));
+    {
+        std::unique_ptr<char[]> buf(new char[N * 16]);   // one array after the other
+        uint32_t* P = reinterpret_cast<uint32_t*>(buf.get());
+        float* V = reinterpret_cast<float*>(buf.get());
+        for (size_t q = 0; q < N; ++q) {
+            const int32_t i = order[q];
+            P[4 * q] = xi[i];
+            P[4 * q + 1] = yi[i];
+            memcpy(&P[4 * q + 2], &r[i], 4);
+            P[4 * q + 3] = (uint32_t)i;
+        }
+        GD_TRY(g, hipMemcpy(g->P[0], P, N * 16, hipMemcpyHostToDevice));
+        for (size_t q = 0; q < N; ++q) {
+            const int32_t i = order[q];
+            V[4 * q] = u[i];
+            V[4 * q + 1] = v[i];
+            V[4 * q + 2] = omega ? omega[i] : 0.0f;
+            V[4 * q + 3] = h[i];
+        }
+        GD_TRY(g, hipMemcpy(g->V[0], V, N * 16, hipMemcpyHostToDevice));
+        for (size_t q = 0; q < N; ++q) V[q] = theta ? theta[order[q]] : 0.0f;
+        GD_TRY(g, hipMemcpy(g->th[0], V, N * 4, hipMemcpyHostToDevice));
     }
-    GD_TRY(g, hipMemcpy(g->id[0], order.data(), N * 4, hipMemcpyHostToDevice));
     GD_TRY(g, hipMemcpy(g->key, skey.data(), N * 4, hipMemcpyHostToDevice));
-    GD_TRY(g, hipMemcpy(g->bcount[0], count.data(), nb * 4, hipMemcpyHostToDevice));
-    GD_TRY(g, hipMemsetAsync(g->bcount[1], 0, nb * 4, g->stream));
-    GD_TRY(g, hipMemcpy(g->rcount[0], rows.data(), (size_t)by * 4, hipMemcpyHostToDevice));
+    GD_TRY(g, hipMemcpy(g->bcount, count.data(), nb * 4, hipMemcpyHostToDevice));
+    GD_TRY(g, hipMemcpy(g->rcount, rows.data(), (size_t)by * 4, hipMemcpyHostToDevice));
     GD_TRY(g, hipMemcpy(g->starts[0], start.data(), (nb + 1) * 4, hipMemcpyHostToDevice));
-    GD_TRY(g, hipMemsetAsync(g->rcount[1], 0, (size_t)by * 4, g->stream));
     GD_TRY(g, hipMemsetAsync(g->err_d, 0, 4, g->stream));
-    GD_TRY(g, hipMemsetAsync(g->contacts_d, 0, 8, g->stream));
+    GD_TRY(g, hipMemsetAsync(g->contacts_d, 0, kContactBytes, g->stream));
     GD_TRY(g, hipMemsetAsync(g->fallbacks_d, 0, 8, g->stream));
     GD_TRY(g, hipStreamSynchronize(g->stream));
     g->cur = 0;
     g->sb = 0;
-    g->rb = 0;
     g->steps = 0;
     g->phase_dirty = true;
     g->have_floes = true;
@@ -954,31 +1071,17 @@ sp_status sp_gdem_step(sp_gdem* g, double dt, int64_t nsteps)
     for (int64_t it = 0; it < nsteps; ++it) {
         const int c = g->cur, o = c ^ 1;
         GPull pl;
-        pl.xi = g->xi[c];
-        pl.yi = g->yi[c];
-        pl.u = g->u[c];
-        pl.v = g->v[c];
-        pl.w = g->w[c];
+        pl.P = g->P[c];
+        pl.V = g->V[c];
         pl.th = g->th[c];
-        pl.r = g->r[c];
-        pl.h = g->h[c];
-        pl.id = g->id[c];
-        pl.xo = g->xi[o];
-        pl.yo = g->yi[o];
-        pl.uo = g->u[o];
-        pl.vo = g->v[o];
-        pl.wo = g->w[o];
+        pl.Po = g->P[o];
+        pl.Vo = g->V[o];
         pl.tho = g->th[o];
-        pl.ro = g->r[o];
-        pl.ho = g->h[o];
-        pl.ido = g->id[o];
         pl.key = g->key;
         pl.ostart = g->starts[g->sb];
         pl.nstart = g->starts[g->sb ^ 1];
-        pl.count = g->bcount[g->rb];
-        pl.count_next = g->bcount[g->rb ^ 1];
-        pl.rows = g->rcount[g->rb];
-        pl.rows_next = g->rcount[g->rb ^ 1];
+        pl.count = g->bcount;
+        pl.rows = g->rcount;
         pl.n = n;
         pl.nbx = g->nbx;
         pl.nby = g->nby;
@@ -990,7 +1093,6 @@ sp_status sp_gdem_step(sp_gdem* g, double dt, int64_t nsteps)
         hipLaunchKernelGGL(gstep_kernel, grid, blk, 0, g->stream, gargs(g, dt, o, c));
         GD_TRY(g, hipGetLastError());
         g->sb ^= 1;
-        g->rb ^= 1;
         g->steps++;
     }
     return SP_OK;
@@ -1002,12 +1104,15 @@ sp_status sp_gdem_read_floes(sp_gdem* g, uint32_t* xi, uint32_t* yi, float* u, f
     if (!g) return SP_EINVAL;
     if (!g->have_floes) return gfail(g, SP_ESTATE, "no floes");
     const int n = (int)g->n, c = g->cur, o = c ^ 1;
-    hipLaunchKernelGGL(gscatter_kernel, dim3((n + 255) / 256), dim3(256), 0, g->stream, g->id[c], n, g->xi[c],
-                       g->yi[c], g->u[c], g->v[c], g->w[c], g->th[c], g->r[c], g->xi[o], g->yi[o], g->u[o], g->v[o],
-                       g->w[o], g->th[o], g->r[o]);
+    // into the arrays of the other buffer, one after the other
+    uint32_t* s0 = reinterpret_cast<uint32_t*>(g->P[o]);
+    float* s1 = reinterpret_cast<float*>(g->V[o]);
+    const size_t N = (size_t)n;
+    hipLaunchKernelGGL(gscatter_kernel, dim3((n + 255) / 256), dim3(256), 0, g->stream, n, g->P[c], g->V[c], g->th[c],
+                       s0, s0 + N, s1, s1 + N, s1 + 2 * N, s1 + 3 * N, g->th[o]);
     GD_TRY(g, hipGetLastError());
     void* dst[7] = {xi, yi, u, v, omega, theta, r};
-    const void* src[7] = {g->xi[o], g->yi[o], g->u[o], g->v[o], g->w[o], g->th[o], g->r[o]};
+    const void* src[7] = {s0, s0 + N, s1, s1 + N, s1 + 2 * N, s1 + 3 * N, g->th[o]};
     for (int k = 0; k < 7; ++k)
         if (dst[k]) GD_TRY(g, hipMemcpyAsync(dst[k], src[k], (size_t)n * 4, hipMemcpyDeviceToHost, g->stream));
     GD_TRY(g, hipStreamSynchronize(g->stream));
@@ -1041,11 +1146,12 @@ sp_status sp_gdem_coarse_moments(sp_gdem* g, int32_t nxc, int32_t nyc, double* o
     }
     GD_TRY(g, hipMemsetAsync(g->ccount, 0, (size_t)ncoarse * 4, g->stream));
     GD_TRY(g, hipMemsetAsync(g->crow, 0, (size_t)nyc * 4, g->stream));
-    hipLaunchKernelGGL(ckey_kernel, dim3((n + 255) / 256), dim3(256), 0, g->stream, g->xi[c], g->yi[c], n, nxc, nyc,
-                       g->ckey, g->ccount, g->crow);
+    hipLaunchKernelGGL(ckey_kernel, dim3((n + 255) / 256), dim3(256), 0, g->stream, g->P[c], n, nxc, nyc, g->ckey, g->ccount, g->crow);
     GD_TRY(g, hipGetLastError());
-    hipLaunchKernelGGL(cpull_kernel, dim3(nyc), dim3(256), 0, g->stream, g->ckey, g->ccount, g->crow,
-                       g->starts[g->sb], n, g->nbx, g->nby, nxc, nyc, g->cstart, g->perm, g->err_d,
+    const int run = ncoarse <= kCoarseSmall ? kCoarseRun : kCoarseRunLarge;
+    const int64_t runs = (int64_t)nyc * ((nxc + run - 1) / run);
+    hipLaunchKernelGGL(cpull_kernel, dim3((unsigned)runs), dim3(256), 0, g->stream, g->ckey, g->ccount, g->crow,
+                       g->starts[g->sb], n, g->nbx, g->nby, nxc, nyc, run, g->cstart, g->perm, g->err_d,
                        g->fallbacks_d);
     GD_TRY(g, hipGetLastError());
     hipLaunchKernelGGL(cmom_kernel, dim3(ncoarse), dim3(64), 0, g->stream, gargs(g, 0.0, c, c ^ 1), g->perm,
@@ -1061,7 +1167,12 @@ sp_status sp_gdem_read_order(sp_gdem* g, int32_t* ids, int32_t* starts, int64_t*
     if (!g) return SP_EINVAL;
     if (!g->have_floes) return gfail(g, SP_ESTATE, "no floes");
     const size_t N = (size_t)g->n, nb = (size_t)g->nbx * g->nby;
-    if (ids) GD_TRY(g, hipMemcpyAsync(ids, g->id[g->cur], N * 4, hipMemcpyDeviceToHost, g->stream));
+    if (ids) {
+        int32_t* s = reinterpret_cast<int32_t*>(g->P[g->cur ^ 1]);
+        hipLaunchKernelGGL(gids_kernel, dim3((unsigned)((N + 255) / 256)), dim3(256), 0, g->stream, (int)N, g->P[g->cur], s);
+        GD_TRY(g, hipGetLastError());
+        GD_TRY(g, hipMemcpyAsync(ids, s, N * 4, hipMemcpyDeviceToHost, g->stream));
+    }
     if (starts) GD_TRY(g, hipMemcpyAsync(starts, g->starts[g->sb], (nb + 1) * 4, hipMemcpyDeviceToHost, g->stream));
     unsigned long long fb = 0;
     GD_TRY(g, hipMemcpyAsync(&fb, g->fallbacks_d, 8, hipMemcpyDeviceToHost, g->stream));
@@ -1073,9 +1184,10 @@ sp_status sp_gdem_read_order(sp_gdem* g, int32_t* ids, int32_t* starts, int64_t*
 sp_status sp_gdem_get_stats(sp_gdem* g, int64_t* contacts, int64_t* steps, int32_t* bins_x, int32_t* bins_y)
 {
     if (!g) return SP_EINVAL;
-    unsigned long long cnt = 0;
-    GD_TRY(g, hipMemcpyAsync(&cnt, g->contacts_d, 8, hipMemcpyDeviceToHost, g->stream));
+    unsigned long long slots[kContactSlots * kContactStride], cnt = 0;
+    GD_TRY(g, hipMemcpyAsync(slots, g->contacts_d, kContactBytes, hipMemcpyDeviceToHost, g->stream));
     GD_TRY(g, hipStreamSynchronize(g->stream));
+    for (int i = 0; i < kContactSlots; ++i) cnt += slots[i * kContactStride];
     if (contacts) *contacts = (int64_t)cnt;
     if (steps) *steps = g->steps;
     if (bins_x) *bins_x = g->nbx;
