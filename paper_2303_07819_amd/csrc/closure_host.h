@@ -353,6 +353,7 @@ __global__ __launch_bounds__(256) void column_stats_kernel(const float* X, long 
 }  // namespace spdem
 
 struct sp_mlp {
+    Staging staging;             // read-outs
     hipStream_t stream = nullptr;
     bool own_stream = false;
     int num_cus = 256;           // compute units of the device (grid of the fused forward)
@@ -412,6 +413,15 @@ sp_status mfail(sp_mlp* m, sp_status st, const char* fmt, ...)
             return mfail((mm), SP_EDEVICE, "%s: %s", #expr, hipGetErrorString(e_));           \
         }                                                                                     \
     } while (0)
+
+// Waits for the stream.
+sp_status mlp_read(sp_mlp* mm, Readout& rd)
+{
+    hipError_t he;
+    (void)rd.run(mm->staging, mm->stream, he);
+    MLP_HIP(mm, he);
+    return SP_OK;
+}
 
 template <class T>
 sp_status malloc_m(sp_mlp* mm, T** p, size_t count)
@@ -597,6 +607,7 @@ sp_status sp_mlp_create(void* stream, sp_mlp** out)
     if (!st) st = malloc_m(mm, &mm->grad, kNParams);
     if (!st) st = malloc_m(mm, &mm->norm, 2 * kIn + 3 * kOut);
     if (!st) st = malloc_m(mm, &mm->loss_d, 1);
+    if (!st) (void)mm->staging.reserve(kNParams * 4 + 64);
     if (!st) {
         std::vector<float> nrm(2 * kIn + 3 * kOut, 0.0f);
         for (int i = 0; i < kIn; ++i) nrm[kIn + i] = 1.0f;
@@ -624,6 +635,7 @@ void sp_mlp_destroy(sp_mlp* mm)
                   mm->aug_x, mm->aug_t};
     for (void* p : ps)
         if (p) (void)hipFree(p);
+    mm->staging.release();
     if (mm->own_stream && mm->stream) (void)hipStreamDestroy(mm->stream);
     delete mm;
 }
@@ -651,9 +663,9 @@ sp_status sp_mlp_set_params(sp_mlp* mm, const float* params)
 sp_status sp_mlp_get_params(sp_mlp* mm, float* params)
 {
     if (!mm || !params) return mm ? mfail(mm, SP_EINVAL, "null output") : SP_EINVAL;
-    MLP_HIP(mm, hipMemcpyAsync(params, mm->theta, kNParams * 4, hipMemcpyDeviceToHost, mm->stream));
-    MLP_HIP(mm, hipStreamSynchronize(mm->stream));
-    return SP_OK;
+    Readout rd;
+    rd.add(params, mm->theta, kNParams, false);
+    return mlp_read(mm, rd);
 }
 
 sp_status sp_mlp_set_norm(sp_mlp* mm, const float* x_mean, const float* x_std, const float* y_mean,
@@ -728,10 +740,11 @@ sp_status sp_mlp_gradient(sp_mlp* mm, const float* X, const float* T, int32_t B,
 {
     if (!mm || !X || !T || B < 1 || !grad_host) return mm ? mfail(mm, SP_EINVAL, "bad gradient arguments") : SP_EINVAL;
     SP_TRY(fused_step(mm, X, T, nullptr, B, false, 0.0f, mm->loss_d));
-    MLP_HIP(mm, hipMemcpyAsync(grad_host, mm->grad, kNParams * 4, hipMemcpyDeviceToHost, mm->stream));
     float ls = 0.0f;
-    MLP_HIP(mm, hipMemcpyAsync(&ls, mm->loss_d, 4, hipMemcpyDeviceToHost, mm->stream));
-    MLP_HIP(mm, hipStreamSynchronize(mm->stream));
+    Readout rd;
+    rd.add(grad_host, mm->grad, kNParams, false);
+    rd.add(&ls, mm->loss_d, 1, false);
+    SP_TRY(mlp_read(mm, rd));
     if (loss) *loss = ls / (float)(B * kOut);
     return SP_OK;
 }
@@ -747,8 +760,9 @@ sp_status sp_mlp_train_step(sp_mlp* mm, const float* X, const float* T, const in
     SP_TRY(fused_step(mm, X, T, rows, B, true, lr, mm->loss_d));
     if (loss) {
         float ls = 0.0f;
-        MLP_HIP(mm, hipMemcpyAsync(&ls, mm->loss_d, 4, hipMemcpyDeviceToHost, mm->stream));
-        MLP_HIP(mm, hipStreamSynchronize(mm->stream));
+        Readout rd;
+        rd.add(&ls, mm->loss_d, 1, false);
+        SP_TRY(mlp_read(mm, rd));
         *loss = ls / (float)(B * kOut);
     }
     return SP_OK;
@@ -790,9 +804,11 @@ sp_status sp_mlp_train_epoch(sp_mlp* mm, const float* X, const float* T, const i
     }
     if (!st && mean_loss) {
         losses.resize((size_t)std::max<int64_t>(nb, 1));
-        if (hipMemcpyAsync(losses.data(), lbuf, losses.size() * 4, hipMemcpyDeviceToHost, mm->stream) != hipSuccess ||
-            hipStreamSynchronize(mm->stream) != hipSuccess)
-            st = SP_EDEVICE;
+        Readout rd;
+        rd.add(losses.data(), lbuf, losses.size(), false);
+        hipError_t he;
+        (void)rd.run(mm->staging, mm->stream, he);
+        if (he != hipSuccess) st = SP_EDEVICE;
         double s = 0.0;
         for (int64_t b = 0; b < nb; ++b) s += losses[b];
         *mean_loss = nb > 0 ? (float)(s / (double)nb / (double)(batch * kOut)) : 0.0f;

@@ -159,8 +159,11 @@ sp_status coarse_step(sp_ctx* c, double dt)
                        c->cell_start, c->r, c->cpl_x0, c->Q[0], c->ncells, inv_area, c->cpl_rreq);
     HIP_TRY(c, hipGetLastError());
     unsigned int bits = 0;
-    HIP_TRY(c, hipMemcpyAsync(&bits, c->cpl_rreq, sizeof bits, hipMemcpyDeviceToHost, c->stream));
-    HIP_TRY(c, hipStreamSynchronize(c->stream));
+    hipError_t he;
+    Readout rd;
+    rd.add(&bits, c->cpl_rreq, 1, false);
+    (void)rd.run(c->staging, c->stream, he);
+    HIP_TRY(c, he);
     float req;
     memcpy(&req, &bits, sizeof req);
     return plan_for_radius(c, req);

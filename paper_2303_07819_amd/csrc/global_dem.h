@@ -67,6 +67,7 @@ struct sp_gdem {
     uint32_t* err_d = nullptr;
     unsigned long long* contacts_d = nullptr;   // [kContactSlots x kContactStride], their sum counts
     int64_t steps = 0;
+    Staging staging;                   // read-outs
 };
 
 namespace spdem {
@@ -883,16 +884,25 @@ sp_status gupload_phase(sp_gdem* g)
     return SP_OK;
 }
 
-sp_status gcheck(sp_gdem* g)
+sp_status gerr(sp_gdem* g, uint32_t e)
 {
-    uint32_t e = 0;
-    GD_TRY(g, hipMemcpyAsync(&e, g->err_d, 4, hipMemcpyDeviceToHost, g->stream));
-    GD_TRY(g, hipStreamSynchronize(g->stream));
     if (e & kErrOverlap) return gfail(g, SP_EOVERLAP, "two floe centres coincide");
     if (e & kErrNaN) return gfail(g, SP_ENAN, "non-finite floe state");
     if (e & kErrWall) return gfail(g, SP_EWALL, "a floe crossed a wall");
     if (e & kErrRebin) return gfail(g, SP_EDEVICE, "re-binning gathered another number of floes than it counted");
     return SP_OK;
+}
+
+// Waits for the stream.
+sp_status gcheck(sp_gdem* g)
+{
+    uint32_t e = 0;
+    hipError_t he;
+    Readout rd;
+    rd.add(&e, g->err_d, 1, false);
+    (void)rd.run(g->staging, g->stream, he);
+    GD_TRY(g, he);
+    return gerr(g, e);
 }
 
 }  // namespace
@@ -928,6 +938,7 @@ sp_status sp_gdem_create(const sp_gdem_params* p, void* stream, sp_gdem** out)
         delete g;
         return st;
     }
+    (void)g->staging.reserve(2 * kStagingStep);
     *out = g;
     return SP_OK;
 }
@@ -937,6 +948,7 @@ void sp_gdem_destroy(sp_gdem* g)
     if (!g) return;
     (void)hipStreamSynchronize(g->stream);
     gdem_free(g);
+    g->staging.release();
     if (g->own_stream) (void)hipStreamDestroy(g->stream);
     delete g;
 }
@@ -1108,15 +1120,20 @@ sp_status sp_gdem_read_floes(sp_gdem* g, uint32_t* xi, uint32_t* yi, float* u, f
     uint32_t* s0 = reinterpret_cast<uint32_t*>(g->P[o]);
     float* s1 = reinterpret_cast<float*>(g->V[o]);
     const size_t N = (size_t)n;
+    uint32_t e = 0;
+    hipError_t he;
+    Readout rd;
     hipLaunchKernelGGL(gscatter_kernel, dim3((n + 255) / 256), dim3(256), 0, g->stream, n, g->P[c], g->V[c], g->th[c],
                        s0, s0 + N, s1, s1 + N, s1 + 2 * N, s1 + 3 * N, g->th[o]);
     GD_TRY(g, hipGetLastError());
     void* dst[7] = {xi, yi, u, v, omega, theta, r};
     const void* src[7] = {s0, s0 + N, s1, s1 + N, s1 + 2 * N, s1 + 3 * N, g->th[o]};
     for (int k = 0; k < 7; ++k)
-        if (dst[k]) GD_TRY(g, hipMemcpyAsync(dst[k], src[k], (size_t)n * 4, hipMemcpyDeviceToHost, g->stream));
-    GD_TRY(g, hipStreamSynchronize(g->stream));
-    return gcheck(g);
+        if (dst[k]) rd.add(dst[k], src[k], N, false);
+    rd.add(&e, g->err_d, 1, false);
+    (void)rd.run(g->staging, g->stream, he);
+    GD_TRY(g, he);
+    return gerr(g, e);
 }
 
 sp_status sp_gdem_coarse_moments(sp_gdem* g, int32_t nxc, int32_t nyc, double* out)
@@ -1157,9 +1174,14 @@ sp_status sp_gdem_coarse_moments(sp_gdem* g, int32_t nxc, int32_t nyc, double* o
     hipLaunchKernelGGL(cmom_kernel, dim3(ncoarse), dim3(64), 0, g->stream, gargs(g, 0.0, c, c ^ 1), g->perm,
                        g->cstart, ncoarse, g->cmom);
     GD_TRY(g, hipGetLastError());
-    GD_TRY(g, hipMemcpyAsync(out, g->cmom, (size_t)ncoarse * SP_NMOM * 8, hipMemcpyDeviceToHost, g->stream));
-    GD_TRY(g, hipStreamSynchronize(g->stream));
-    return gcheck(g);
+    uint32_t e = 0;
+    hipError_t he;
+    Readout rd;
+    rd.add(out, g->cmom, (size_t)ncoarse * SP_NMOM, true);
+    rd.add(&e, g->err_d, 1, false);
+    (void)rd.run(g->staging, g->stream, he);
+    GD_TRY(g, he);
+    return gerr(g, e);
 }
 
 sp_status sp_gdem_read_order(sp_gdem* g, int32_t* ids, int32_t* starts, int64_t* fallbacks)
@@ -1185,14 +1207,19 @@ sp_status sp_gdem_get_stats(sp_gdem* g, int64_t* contacts, int64_t* steps, int32
 {
     if (!g) return SP_EINVAL;
     unsigned long long slots[kContactSlots * kContactStride], cnt = 0;
-    GD_TRY(g, hipMemcpyAsync(slots, g->contacts_d, kContactBytes, hipMemcpyDeviceToHost, g->stream));
-    GD_TRY(g, hipStreamSynchronize(g->stream));
+    uint32_t e = 0;
+    hipError_t he;
+    Readout rd;
+    rd.add(slots, g->contacts_d, kContactSlots * kContactStride, true);
+    rd.add(&e, g->err_d, 1, false);
+    (void)rd.run(g->staging, g->stream, he);
+    GD_TRY(g, he);
     for (int i = 0; i < kContactSlots; ++i) cnt += slots[i * kContactStride];
     if (contacts) *contacts = (int64_t)cnt;
     if (steps) *steps = g->steps;
     if (bins_x) *bins_x = g->nbx;
     if (bins_y) *bins_y = g->nby;
-    return gcheck(g);
+    return gerr(g, e);
 }
 
 }  // extern "C"

@@ -382,12 +382,15 @@ sp_status hybrid_check(sp_ctx* c, double dt)
     HIP_TRY(c, hipGetLastError());
     SP_TRY(net_forward_on(c, h->net, h->Xk, nk, h->Tk));
     std::vector<float> tm((size_t)nk * 4), td((size_t)nk * 4), xk((size_t)nk * spmlp::kIn);
-    HIP_TRY(c, hipMemcpyAsync(tm.data(), h->Tk, tm.size() * 4, hipMemcpyDeviceToHost, c->stream));
-    HIP_TRY(c, hipMemcpyAsync(td.data(), h->Tdem, td.size() * 4, hipMemcpyDeviceToHost, c->stream));
-    HIP_TRY(c, hipMemcpyAsync(xk.data(), h->Xk, xk.size() * 4, hipMemcpyDeviceToHost, c->stream));
     // 4. the reduced DEMs restart from the true floes
     SP_TRY(restart_reduced(c, h->chk_d, nk, nullptr));
-    HIP_TRY(c, hipStreamSynchronize(c->stream));
+    hipError_t he;
+    Readout rd;
+    rd.add(tm.data(), h->Tk, tm.size(), false);
+    rd.add(td.data(), h->Tdem, td.size(), false);
+    rd.add(xk.data(), h->Xk, xk.size(), false);
+    (void)rd.run(c->staging, c->stream, he);
+    HIP_TRY(c, he);
     // the cell's own state is feature 16..19 (centre of the 3 x 3 stencil)
     double floor[4] = {0, 0, 0, 0};
     for (int i = 0; i < nk; ++i)

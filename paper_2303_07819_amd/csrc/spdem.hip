@@ -35,6 +35,7 @@
 #include "../../include/spdem.h"
 #include "dem_kernels.h"
 #include "block_kernels.h"
+#include "readout.h"
 
 using namespace spdem;
 
@@ -106,6 +107,7 @@ struct sp_ctx {
     ModeC* modec = nullptr;                 // [ncells][nmodes]: mode constants of every cell (blocked launches)
     double* ocen = nullptr;                 // [ncells][4]: ocean u, v and curl at each cell centre, 0
     double* momb[2] = {nullptr, nullptr};   // statistics of time level k in momb[k & 1]
+    Staging staging;                        // read-outs
     double* mom2 = nullptr;                 // statistics of the current state (read_moments)
     double* Q[2] = {nullptr, nullptr};      // continuum of time level k in Q[k & 1]
     uint32_t* err_d = nullptr;
@@ -447,17 +449,26 @@ sp_status invalidate_lists(sp_ctx* c, const int32_t* cells_d, int n)
     return SP_OK;
 }
 
-sp_status check_device_err(sp_ctx* c)
+sp_status device_err(sp_ctx* c, uint32_t e)
 {
-    uint32_t e = 0;
-    HIP_TRY(c, hipMemcpyAsync(&e, c->err_d, sizeof e, hipMemcpyDeviceToHost, c->stream));
-    HIP_TRY(c, hipStreamSynchronize(c->stream));
     if (!e) return SP_OK;
     if (e & kErrOverlap) return fail(c, SP_EOVERLAP, "coincident floe centres in contact");
     if (e & kErrNaN) return fail(c, SP_ENAN, "non-finite floe state");
     if (e & kErrCapacity) return fail(c, SP_ECAPACITY, "more than %d contacts on one floe", kListCap);
     if (e & kErrWall) return fail(c, SP_EWALL, "a floe crossed a wall");
     return fail(c, SP_ECFL, "continuum CFL number exceeded 1");
+}
+
+// Waits for the stream.
+sp_status check_device_err(sp_ctx* c)
+{
+    uint32_t e = 0;
+    Readout rd;
+    rd.add(&e, c->err_d, 1, false);
+    hipError_t he;
+    (void)rd.run(c->staging, c->stream, he);
+    HIP_TRY(c, he);
+    return device_err(c, e);
 }
 
 // --------------------------------------------------------- kernel launches
@@ -1134,6 +1145,7 @@ sp_status sp_create(const sp_params* params, void* stream, sp_ctx** out)
     if (!st) st = dalloc(c, &c->momb[0], (size_t)c->ncells * kMomStride);
     if (!st) st = dalloc(c, &c->momb[1], (size_t)c->ncells * kMomStride);
     if (!st) st = dalloc(c, &c->mom2, (size_t)c->ncells * kMomStride);
+    if (!st) (void)c->staging.reserve(std::min((size_t)c->ncells * SP_NMOM * 8 + 64, kStagingMax));
     if (!st) st = dalloc(c, &c->Q[0], (size_t)c->ncells * 4);
     if (!st) st = dalloc(c, &c->Q[1], (size_t)c->ncells * 4);
     if (!st && hipMemsetAsync(c->err_d, 0, sizeof(uint32_t), c->stream) != hipSuccess) st = SP_EDEVICE;
@@ -1163,6 +1175,7 @@ void sp_destroy(sp_ctx* c)
     if (c->bk_join) (void)hipEventDestroy(c->bk_join);
     if (c->bk_stream) (void)hipStreamDestroy(c->bk_stream);
     free_all(c);
+    c->staging.release();
     if (c->own_stream && c->stream) (void)hipStreamDestroy(c->stream);
     delete c;
 }
@@ -1518,6 +1531,15 @@ sp_status sp_read_moments(sp_ctx* c, int32_t which, double* out)
             hipLaunchKernelGGL(stats_kernel, dim3(nc), dim3(256), 0, c->stream, a, nullptr, 0);
             HIP_TRY(c, hipGetLastError());
         }
+        uint32_t e = 0;
+        hipError_t he;
+        Readout rd;
+        rd.add(out, c->mom2, (size_t)nc * SP_NMOM, true, SP_NMOM, kMomStride, 1);
+        rd.add(&e, c->err_d, 1, false);
+        if (rd.run(c->staging, c->stream, he)) {
+            HIP_TRY(c, he);
+            return device_err(c, e);
+        }
         std::vector<double> buf((size_t)nc * kMomStride);
         HIP_TRY(c, hipMemcpyAsync(buf.data(), c->mom2, buf.size() * 8, hipMemcpyDeviceToHost, c->stream));
         HIP_TRY(c, hipStreamSynchronize(c->stream));
@@ -1525,6 +1547,15 @@ sp_status sp_read_moments(sp_ctx* c, int32_t which, double* out)
             for (int k = 0; k < SP_NMOM; ++k) out[(size_t)i * SP_NMOM + k] = buf[(size_t)i * kMomStride + k];
     } else if (which == SP_MOMENTS_CONTINUUM) {
         SP_TRY(flush_lf(c));
+        uint32_t e = 0;
+        hipError_t he;
+        Readout rd;
+        rd.add(out, c->Q[c->kstep & 1], (size_t)nc * 4, true, 4, 1, (uint32_t)nc);
+        rd.add(&e, c->err_d, 1, false);
+        if (rd.run(c->staging, c->stream, he)) {
+            HIP_TRY(c, he);
+            return device_err(c, e);
+        }
         std::vector<double> buf((size_t)nc * 4);
         HIP_TRY(c, hipMemcpyAsync(buf.data(), c->Q[c->kstep & 1], buf.size() * 8, hipMemcpyDeviceToHost,
                                   c->stream));
@@ -1576,13 +1607,17 @@ sp_status sp_read_floes(sp_ctx* c, uint32_t* xi, uint32_t* yi, float* u, float* 
 {
     if (!c) return SP_EINVAL;
     if (!c->have_floes) return fail(c, SP_ESTATE, "no floes");
-    const size_t N = (size_t)c->n * 4;
     void* dst[7] = {xi, yi, u, v, omega, theta, r};
     const void* src[7] = {c->xi, c->yi, c->u, c->v, c->w, c->th, c->r};
+    uint32_t e = 0;
+    hipError_t he;
+    Readout rd;
     for (int k = 0; k < 7; ++k)
-        if (dst[k] && N) HIP_TRY(c, hipMemcpyAsync(dst[k], src[k], N, hipMemcpyDeviceToHost, c->stream));
-    HIP_TRY(c, hipStreamSynchronize(c->stream));
-    return check_device_err(c);
+        if (dst[k]) rd.add(dst[k], src[k], (size_t)c->n, false);
+    rd.add(&e, c->err_d, 1, false);
+    (void)rd.run(c->staging, c->stream, he);
+    HIP_TRY(c, he);
+    return device_err(c, e);
 }
 
 sp_status sp_read_pairs(sp_ctx* c, int64_t cap, int32_t* l, int32_t* j, int64_t* count)
@@ -1638,10 +1673,12 @@ sp_status sp_get_stats(sp_ctx* c, int64_t* contacts, int64_t* steps, double* max
     if (c->have_floes) SP_TRY(flush_lf(c));
     unsigned long long cnt = 0, bits = 0;
     std::vector<unsigned long long> per_cell((size_t)c->ncells);
-    HIP_TRY(c, hipMemcpyAsync(per_cell.data(), c->contacts_d, per_cell.size() * 8, hipMemcpyDeviceToHost,
-                              c->stream));
-    HIP_TRY(c, hipMemcpyAsync(&bits, c->cfl_bits_d, 8, hipMemcpyDeviceToHost, c->stream));
-    HIP_TRY(c, hipStreamSynchronize(c->stream));
+    hipError_t he;
+    Readout rd;
+    rd.add(per_cell.data(), c->contacts_d, per_cell.size(), true);
+    rd.add(&bits, c->cfl_bits_d, 1, true);
+    (void)rd.run(c->staging, c->stream, he);
+    HIP_TRY(c, he);
     for (unsigned long long x : per_cell) cnt += x;
     if (contacts) *contacts = (int64_t)cnt;
     if (steps) *steps = c->steps;
