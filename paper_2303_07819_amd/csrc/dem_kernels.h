@@ -650,29 +650,38 @@ __device__ __forceinline__ double lf_operand(int C, int t, const double* mom, co
     return cell < 0 ? 0.0 : mom[(size_t)cell * kMomStride + slot];
 }
 
-__device__ __forceinline__ void lf_from_ops(int C, const double* o, double* Qn, int nc, double dT, double dX,
-                                            double dY, double inv_area, unsigned long long* max_cfl_bits,
-                                            uint32_t* err)
+// The updated state qn[4]; returns the cell's CFL number.  The fused products
+// are written out: every kernel rounds alike.
+__device__ __forceinline__ double lf_update(const double* o, double* qn, double dT, double dX, double dY,
+                                            double inv_area)
 {
+#pragma clang fp contract(off)
     const double uE = o[16], uW = o[17], vN = o[18], vS = o[19], uC = o[20], vC = o[21];
     const double cx = dT / (2.0 * dX), cy = dT / (2.0 * dY);
 #pragma unroll
     for (int f = 0; f < 4; ++f) {
         const double qE = o[4 * f], qW = o[4 * f + 1];
         const double qN = o[4 * f + 2], qS = o[4 * f + 3];
-        const double avg = 0.25 * (qE + qW + qN + qS);
-        double q;
-        if (f == 0) {
-            q = avg - cx * (uE * qE - uW * qW) - cy * (vN * qN - vS * qS);
-        } else if (f == 3) {
-            q = avg - cx * (uE * qE - uW * qW) - cy * (vN * qN - vS * qS) + dT * o[22] * inv_area;
+        const double sum = qE + qW + qN + qS;
+        if (f == 0 || f == 3) {
+            const double fx = fma(qE, uE, -(qW * uW)), fy = fma(qN, vN, -(qS * vS));
+            qn[f] = fma(-cy, fy, fma(sum, 0.25, -(cx * fx)));
         } else {
-            q = avg - dT * (uC * (qE - qW) / (2.0 * dX) + vC * (qN - qS) / (2.0 * dY)) +
-                dT * o[f == 1 ? 23 : 24] * inv_area;
+            qn[f] = fma(sum, 0.25, -(dT * (uC * (qE - qW) / (2.0 * dX) + vC * (qN - qS) / (2.0 * dY))));
         }
-        Qn[(size_t)f * nc + C] = q;
+        if (f) qn[f] = fma(inv_area, dT * o[f == 1 ? 23 : f == 2 ? 24 : 22], qn[f]);
     }
-    const double cfl = fabs(uC) * dT / dX + fabs(vC) * dT / dY;
+    return fabs(uC) * dT / dX + fabs(vC) * dT / dY;
+}
+
+__device__ __forceinline__ void lf_from_ops(int C, const double* o, double* Qn, int nc, double dT, double dX,
+                                            double dY, double inv_area, unsigned long long* max_cfl_bits,
+                                            uint32_t* err)
+{
+    double q[4];
+    const double cfl = lf_update(o, q, dT, dX, dY, inv_area);
+#pragma unroll
+    for (int f = 0; f < 4; ++f) Qn[(size_t)f * nc + C] = q[f];
     const unsigned long long bits = (unsigned long long)__double_as_longlong(cfl);
     if (bits > *max_cfl_bits) atomicMax(max_cfl_bits, bits);
     if (cfl > 1.0) atomicOr(err, kErrCFL);
@@ -1174,6 +1183,117 @@ __global__ __launch_bounds__(64) void lf_kernel(CellStats st, const double* Q, d
 {
     const int C = blockIdx.x * blockDim.x + threadIdx.x;
     if (C < nx * ny) lf_cell(C, st, Q, Qn, nx, ny, dT, dX, dY, inv_area, max_cfl_bits, err, wall != 0);
+}
+
+// S continuum steps per launch, the statistics of step s in slot s of a blocked
+// launch's ring.  A step is a launch's own time (3.2 to 5 us) whatever the grid
+// up to 128 x 128 cells: here a workgroup keeps its cells' state in LDS over
+// the steps, one cell per thread, the next step's statistics read ahead.
+// WHOLE: one workgroup holds the grid (up to kLfWhole cells), for any S.
+// Otherwise a workgroup owns kLfTile x kLfTile cells and computes kLfHalo more
+// on every side, of which each step invalidates one: S <= kLfHalo.  The tile is
+// as small as it is because 256 threads, one wavefront per SIMD, take the
+// shortest step, and idle compute units do the halos' repeated work for nothing
+// (64 x 64 cells: 121 workgroups).  Q and Qn differ unless WHOLE.  A step's chain
+// of FP64 divisions bounds it.  Five steps on 64 x 64 cells 7.9 us, 23 before;
+// 20 steps on 4 x 4 cells 12.7 us, 64 before.  Reading the statistics of five
+// steps together made no difference (8.1).
+constexpr int kLfWhole = 512;
+constexpr int kLfSide = 16, kLfHalo = 5, kLfTile = kLfSide - 2 * kLfHalo;
+
+template <bool WHOLE>
+__global__ __launch_bounds__(WHOLE ? kLfWhole : kLfSide* kLfSide) void lf_steps_kernel(
+    const double* ring, size_t slot, int S, const double* Q, double* Qn, int nx, int ny, double dT, double dX,
+    double dY, double inv_area, unsigned long long* max_cfl_bits, uint32_t* err, int wall)
+{
+    constexpr int N = WHOLE ? kLfWhole : kLfSide * kLfSide;
+    __shared__ double q[2][4][N + 1], uv[2][2][N + 1];   // entry N: the ghost cell beyond a wall
+    const int tid = threadIdx.x, nc = nx * ny;
+    int C, iE, iW, iN, iS;
+    bool own, ghost = false;
+    if (WHOLE) {
+        own = tid < nc;
+        C = own ? tid : 0;
+        const LfNeighbours b = lf_neighbours(C, nx, ny, wall != 0);
+        iE = b.E < 0 ? N : b.E;
+        iW = b.W < 0 ? N : b.W;
+        iN = b.N;
+        iS = b.S;
+    } else {
+        const int tiles = (nx + kLfTile - 1) / kLfTile;
+        const int lx = tid % kLfSide, ly = tid / kLfSide;
+        const int x = (int)(blockIdx.x % tiles) * kLfTile + lx - kLfHalo;
+        const int y = (int)(blockIdx.x / tiles) * kLfTile + ly - kLfHalo;
+        ghost = wall && (x < 0 || x >= nx);
+        own = lx >= kLfHalo && lx < kLfHalo + kLfTile && ly >= kLfHalo && ly < kLfHalo + kLfTile && x < nx && y < ny;
+        const int xw = x % nx, yw = y % ny;
+        C = (yw < 0 ? yw + ny : yw) * nx + (xw < 0 ? xw + nx : xw);
+        iE = lx + 1 < kLfSide ? tid + 1 : tid;
+        iW = lx > 0 ? tid - 1 : tid;
+        iN = ly + 1 < kLfSide ? tid + kLfSide : tid;
+        iS = ly > 0 ? tid - kLfSide : tid;
+    }
+    const bool live = !ghost && (WHOLE ? own : true);
+    double qn[4];
+#pragma unroll
+    for (int f = 0; f < 4; ++f) {
+        qn[f] = live ? Q[(size_t)f * nc + C] : 0.0;
+        q[0][f][tid] = qn[f];
+    }
+    if (tid < 2) {
+#pragma unroll
+        for (int f = 0; f < 4; ++f) q[tid][f][N] = 0.0;
+        uv[tid][0][N] = uv[tid][1][N] = 0.0;
+    }
+    double ub, vb, sx, sy, sw;
+    auto statistics = [&](int s) {
+        const double* at = ring + (size_t)s * slot + C;
+        ub = live ? at[(size_t)R_UBAR * nc] : 0.0;
+        vb = live ? at[(size_t)R_VBAR * nc] : 0.0;
+        sx = live ? at[(size_t)R_SVX * nc] : 0.0;
+        sy = live ? at[(size_t)R_SVY * nc] : 0.0;
+        sw = live ? at[(size_t)R_SW * nc] : 0.0;
+    };
+    statistics(0);
+    unsigned long long most = 0;
+    bool over = false;
+    for (int s = 0; s < S; ++s) {
+        const int p = s & 1;
+        uv[p][0][tid] = ub;
+        uv[p][1][tid] = vb;
+        double o[kLfOps];
+        o[20] = ub;
+        o[21] = vb;
+        o[22] = sw;
+        o[23] = sx;
+        o[24] = sy;
+        __syncthreads();
+        if (s + 1 < S) statistics(s + 1);
+#pragma unroll
+        for (int f = 0; f < 4; ++f) {
+            o[4 * f] = q[p][f][iE];
+            o[4 * f + 1] = q[p][f][iW];
+            o[4 * f + 2] = q[p][f][iN];
+            o[4 * f + 3] = q[p][f][iS];
+        }
+        o[16] = uv[p][0][iE];
+        o[17] = uv[p][0][iW];
+        o[18] = uv[p][1][iN];
+        o[19] = uv[p][1][iS];
+        const double cfl = lf_update(o, qn, dT, dX, dY, inv_area);
+        const unsigned long long bits = (unsigned long long)__double_as_longlong(cfl);
+        most = bits > most ? bits : most;
+        over = over || cfl > 1.0;
+        // read by the other threads after the next barrier; what they read
+        // before this one's end is the other copy
+#pragma unroll
+        for (int f = 0; f < 4; ++f) q[p ^ 1][f][tid] = ghost ? 0.0 : qn[f];
+    }
+    if (!own) return;
+#pragma unroll
+    for (int f = 0; f < 4; ++f) Qn[(size_t)f * nc + C] = qn[f];
+    if (most > *max_cfl_bits) atomicMax(max_cfl_bits, most);
+    if (over) atomicOr(err, kErrCFL);
 }
 
 // The same update for the listed cells only (the cells without floes, which

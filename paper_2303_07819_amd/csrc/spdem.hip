@@ -802,6 +802,20 @@ bool block_eligible(const sp_ctx* c)
     return true;
 }
 
+// Continuum steps of the next launch of a block's `left`: all of them where one
+// workgroup holds the grid; up to kLfTilesMax cells an odd number within the
+// halo (the launch writes the other buffer, which an odd number of steps ends
+// in); one where the tiles' repeated work is no longer free.
+constexpr int kLfTilesMax = 128 * 128;
+
+int lf_launch_steps(const sp_ctx* c, int left)
+{
+    if (c->ncells <= kLfWhole) return left;
+    if (c->ncells > kLfTilesMax) return 1;
+    const int s = std::min(left, kLfHalo);
+    return s % 2 ? s : s - 1;
+}
+
 // Make the library stream wait for the continuum updates of the last block
 // (they run on a stream of their own, beside the next block's DEM launch).
 sp_status join_block_lf(sp_ctx* c)
@@ -844,8 +858,8 @@ sp_status block_prepare(sp_ctx* c)
 // written again only after its updates are done).  A run shorter than a block
 // is one launch of its own length, so every plain step of an eligible context
 // is blocked.
-sp_status block_chunk(sp_ctx* c, const StepArgs& base, int K, bool time_dem = false, hipEvent_t e0 = nullptr,
-                      hipEvent_t e1 = nullptr)
+sp_status block_chunk(sp_ctx* c, const StepArgs& base, int K, bool last, bool time_dem = false,
+                      hipEvent_t e0 = nullptr, hipEvent_t e1 = nullptr)
 {
     const size_t slot = (size_t)c->ncells * kRing;
     SP_TRY(block_prepare(c));
@@ -861,20 +875,43 @@ sp_status block_chunk(sp_ctx* c, const StepArgs& base, int K, bool time_dem = fa
     if (time_dem) HIP_TRY(c, hipEventRecord(e1, c->stream));
     if (!(c->p.flags & SP_NO_CONTINUUM)) {
         // everything enqueued on the library stream so far (this block's
-        // statistics, earlier continuum work) precedes the updates
-        HIP_TRY(c, hipEventRecord(c->dem_done[r], c->stream));
-        HIP_TRY(c, hipStreamWaitEvent(c->lf_stream, c->dem_done[r], 0));
-        for (int t = 0; t < K; ++t) {
-            const int64_t k = c->kstep + t;
-            hipLaunchKernelGGL(lf_kernel, dim3((c->ncells + 63) / 64), dim3(64), 0, c->lf_stream,
-                               stats_of_slot(ring + t * slot, c->ncells),
-                               c->Q[k & 1], c->Q[(k + 1) & 1], c->p.nx, c->p.ny, base.dtd, c->p.cell_lx,
-                               c->p.cell_ly, base.inv_area, c->cfl_bits_d, c->err_d, wall_x(c));
-            HIP_TRY(c, hipGetLastError());
+        // statistics, earlier continuum work) precedes the updates; the last
+        // block's have no launch to run beside and follow it there
+        const hipStream_t on = last ? c->stream : c->lf_stream;
+        if (last) {
+            SP_TRY(join_block_lf(c));
+        } else {
+            HIP_TRY(c, hipEventRecord(c->dem_done[r], c->stream));
+            HIP_TRY(c, hipStreamWaitEvent(c->lf_stream, c->dem_done[r], 0));
         }
-        HIP_TRY(c, hipEventRecord(c->lf_done[r], c->lf_stream));
-        c->lf_used[r] = true;
-        c->lf_last = r;
+        for (int t = 0; t < K;) {
+            const int64_t k = c->kstep + t;
+            const int S = lf_launch_steps(c, K - t);
+            const double* const from = c->Q[k & 1];
+            double* const to = c->Q[(k + S) & 1];
+            const double* const st = ring + t * slot;
+            if (c->ncells <= kLfWhole)
+                hipLaunchKernelGGL(lf_steps_kernel<true>, dim3(1), dim3((c->ncells + 63) / 64 * 64), 0, on, st,
+                                   slot, S, from, to, c->p.nx, c->p.ny, base.dtd, c->p.cell_lx, c->p.cell_ly,
+                                   base.inv_area, c->cfl_bits_d, c->err_d, wall_x(c));
+            else if (S > 1)
+                hipLaunchKernelGGL(lf_steps_kernel<false>,
+                                   dim3((c->p.nx + kLfTile - 1) / kLfTile * ((c->p.ny + kLfTile - 1) / kLfTile)),
+                                   dim3(kLfSide * kLfSide), 0, on, st, slot, S, from, to, c->p.nx, c->p.ny,
+                                   base.dtd, c->p.cell_lx, c->p.cell_ly, base.inv_area, c->cfl_bits_d, c->err_d,
+                                   wall_x(c));
+            else
+                hipLaunchKernelGGL(lf_kernel, dim3((c->ncells + 63) / 64), dim3(64), 0, on,
+                                   stats_of_slot(st, c->ncells), from, to, c->p.nx, c->p.ny, base.dtd, c->p.cell_lx,
+                                   c->p.cell_ly, base.inv_area, c->cfl_bits_d, c->err_d, wall_x(c));
+            HIP_TRY(c, hipGetLastError());
+            t += S;
+        }
+        if (!last) {
+            HIP_TRY(c, hipEventRecord(c->lf_done[r], c->lf_stream));
+            c->lf_last = r;
+        }
+        c->lf_used[r] = !last;
     }
     c->blk_parity = r ^ 1;
     c->kstep += K;
@@ -1384,27 +1421,6 @@ sp_status sp_set_floes_device(sp_ctx* c, int64_t n, const int32_t* counts, const
     return set_floes_common(c, n, counts, src, hipMemcpyDeviceToDevice);
 }
 
-// A call's continuum updates follow its last blocked launch (each earlier
-// block's run beside the next block's DEM launch).  Ending the call in a short
-// launch of kTailSteps steps lets the updates of the steps before it run
-// beside that launch, and leaves only its own after it; the extra launch costs
-// its staging and write-back.  Measured on MI355X: a continuum launch on a grid
-// of up to kTailMaxCells cells takes about kLfLaunchPs (launch and memory
-// latency, not bandwidth), one more blocked launch about kStagePsPerFloe
-// picoseconds per floe (plain64, 1,048,576 floes in 4096 cells: 27 us, and a
-// 20-step call 3-4 % faster; uneven128, 4.17 M floes in 16,384 cells: 108 us
-// against 30 updates of 2.8 us, slower split, so not split).
-constexpr int kTailSteps = 2;
-constexpr int kTailMaxCells = 16384;
-constexpr double kLfLaunchPs = 2.8e6;
-constexpr double kStagePsPerFloe = 26.0;
-
-static bool tail_split_pays(const sp_ctx* c, int K)
-{
-    if (K < 6 * kTailSteps || c->ncells > kTailMaxCells) return false;
-    return (double)(K - kTailSteps) * kLfLaunchPs > kStagePsPerFloe * (double)c->n;
-}
-
 sp_status sp_step(sp_ctx* c, double dt, int64_t nsteps)
 {
     if (!c) return SP_EINVAL;
@@ -1422,12 +1438,10 @@ sp_status sp_step(sp_ctx* c, double dt, int64_t nsteps)
         // whole blocks, then the remainder as one shorter block: no step of
         // this path runs the per-step kernel or captures a graph
         while (left > 0) {
-            int K = (int)std::min<int64_t>(left, c->block_k);
-            if (K == left && cont && tail_split_pays(c, K)) K -= kTailSteps;
-            SP_TRY(block_chunk(c, base, K));
+            const int K = (int)std::min<int64_t>(left, c->block_k);
             left -= K;
+            SP_TRY(block_chunk(c, base, K, left == 0));
         }
-        SP_TRY(join_block_lf(c));   // later work on the stream sees the continuum
         return SP_OK;
     }
     while (left > 0) {
@@ -1468,7 +1482,7 @@ sp_status sp_profile_steps(sp_ctx* c, double dt, int64_t nsteps, double* dem_ms,
         c->t_now += dt * (double)(chunks * c->block_k);
         sp_status st = SP_OK;
         HIP_TRY(c, hipEventRecord(ev[2 * chunks], c->stream));
-        for (int64_t q = 0; q < chunks && !st; ++q) st = block_chunk(c, base, c->block_k, true, ev[2 * q], ev[2 * q + 1]);
+        for (int64_t q = 0; q < chunks && !st; ++q) st = block_chunk(c, base, c->block_k, false, true, ev[2 * q], ev[2 * q + 1]);
         if (!st) st = join_block_lf(c);
         HIP_TRY(c, hipEventRecord(ev[2 * chunks + 1], c->stream));
         HIP_TRY(c, hipStreamSynchronize(c->stream));
