@@ -159,67 +159,62 @@ struct ClosureArgs {
     int nx, ny;
     double dX, dY;
     double t;       // time of the pre-step state
-    const double* rs;   // [ncells][5] reduced_stats of every cell at t, or null: computed where needed
 };
 
-// The base update of cell C (lf_cell with the reduced DEM statistics of every cell).
-__device__ __forceinline__ void cell_rstats(int C, const ClosureArgs& a, double out[5])
+// The base update (lf_cell with reduced DEM statistics) from the cell's
+// statistics sC, its neighbours' coefficients and states q[4 f + E, W, N, S].
+__device__ __forceinline__ void base_update(const double* sC, double uE, double uW, double vN, double vS,
+                                            const double* q, double dT, double dX, double dY, double out[4])
 {
-    if (a.rs) {
+    const double cx = dT / (2.0 * dX), cy = dT / (2.0 * dY);
 #pragma unroll
-        for (int k = 0; k < 5; ++k) out[k] = a.rs[(size_t)C * 5 + k];
-    } else {
-        reduced_stats(C, a.red, a.mf, a.oc, a.t, out);
+    for (int f = 0; f < 4; ++f) {
+        const double qE = q[4 * f], qW = q[4 * f + 1];
+        const double qN = q[4 * f + 2], qS = q[4 * f + 3];
+        const double avg = 0.25 * (qE + qW + qN + qS);
+        if (f == 0 || f == 3)
+            out[f] = avg - cx * (uE * qE - uW * qW) - cy * (vN * qN - vS * qS) + (f == 3 ? dT * sC[4] : 0.0);
+        else
+            out[f] = avg - dT * (sC[0] * (qE - qW) / (2.0 * dX) + sC[1] * (qN - qS) / (2.0 * dY)) +
+                     dT * sC[f == 1 ? 2 : 3];
+    }
+}
+
+// Coefficient <v> of cell C's reduced DEM at a.t.
+__device__ __forceinline__ void reduced_coefficient(int C, const ClosureArgs& a, double& u, double& v)
+{
+    const CellOcean o = centre_of(C, a.oc);
+    double dux, duy, dw;
+    reduced_rel(C, a.red, a.mf, a.t, dux, duy, dw);
+    u = o.u - dux;
+    v = o.v - duy;
+}
+
+__device__ __forceinline__ void stencil_states(const LfNeighbours& b, const double* Q, int nc, double* q)
+{
+#pragma unroll
+    for (int f = 0; f < 4; ++f) {
+        q[4 * f] = Q[(size_t)f * nc + b.E];
+        q[4 * f + 1] = Q[(size_t)f * nc + b.W];
+        q[4 * f + 2] = Q[(size_t)f * nc + b.N];
+        q[4 * f + 3] = Q[(size_t)f * nc + b.S];
     }
 }
 
 __device__ __forceinline__ void base_cell(int C, const double* Q, const ClosureArgs& a, double dT, double out[4])
 {
-    const int nx = a.nx, ny = a.ny, nc = nx * ny;
-    const int ix = C % nx, iy = C / nx;
-    const int E = iy * nx + (ix + 1 == nx ? 0 : ix + 1);
-    const int W = iy * nx + (ix == 0 ? nx - 1 : ix - 1);
-    const int N = (iy + 1 == ny ? 0 : iy + 1) * nx + ix;
-    const int S = (iy == 0 ? ny - 1 : iy - 1) * nx + ix;
-    double sC[5], sE[5], sW[5], sN[5], sS[5];
-    cell_rstats(C, a, sC);
-    cell_rstats(E, a, sE);
-    cell_rstats(W, a, sW);
-    cell_rstats(N, a, sN);
-    cell_rstats(S, a, sS);
-    const double cx = dT / (2.0 * a.dX), cy = dT / (2.0 * a.dY);
-#pragma unroll
-    for (int f = 0; f < 4; ++f) {
-        const double qE = Q[(size_t)f * nc + E], qW = Q[(size_t)f * nc + W];
-        const double qN = Q[(size_t)f * nc + N], qS = Q[(size_t)f * nc + S];
-        const double avg = 0.25 * (qE + qW + qN + qS);
-        if (f == 0 || f == 3)
-            out[f] = avg - cx * (sE[0] * qE - sW[0] * qW) - cy * (sN[1] * qN - sS[1] * qS) + (f == 3 ? dT * sC[4] : 0.0);
-        else
-            out[f] = avg - dT * (sC[0] * (qE - qW) / (2.0 * a.dX) + sC[1] * (qN - qS) / (2.0 * a.dY)) +
-                     dT * sC[f == 1 ? 2 : 3];
-    }
+    const LfNeighbours b = lf_neighbours(C, a.nx, a.ny, false);
+    double sC[5], q[16], uE, uW, vN, vS, unused;
+    reduced_stats(C, a.red, a.mf, a.oc, a.t, sC);
+    reduced_coefficient(b.E, a, uE, unused);
+    reduced_coefficient(b.W, a, uW, unused);
+    reduced_coefficient(b.N, a, unused, vN);
+    reduced_coefficient(b.S, a, unused, vS);
+    stencil_states(b, Q, a.nx * a.ny, q);
+    base_update(sC, uE, uW, vN, vS, q, dT, a.dX, a.dY, out);
 }
 
 // Base-updated state of every cell: Qb [4][nc].
-// The reduced DEM statistics of every cell at a.t (a.rs must be null).
-// Every cell's reduced statistics into rs; with row, a closure cell (row[C] >=
-// 0) also writes its coefficient <v> into the step's statistics (ub, vb at C *
-// stride), which its DEM neighbours' continuum stencils read.
-__global__ void reduced_stats_kernel(ClosureArgs a, double* rs, const int32_t* row, double* ub, double* vb, int stride)
-{
-    const int C = blockIdx.x * blockDim.x + threadIdx.x;
-    if (C >= a.nx * a.ny) return;
-    double o[5];
-    reduced_stats(C, a.red, a.mf, a.oc, a.t, o);
-#pragma unroll
-    for (int k = 0; k < 5; ++k) rs[(size_t)C * 5 + k] = o[k];
-    if (row && row[C] >= 0) {
-        ub[(size_t)C * stride] = o[0];
-        vb[(size_t)C * stride] = o[1];
-    }
-}
-
 __global__ void base_kernel(const double* Q, double* Qb, ClosureArgs a, double dT)
 {
     const int C = blockIdx.x * blockDim.x + threadIdx.x;
@@ -439,17 +434,29 @@ sp_status malloc_m(sp_mlp* mm, T** p, size_t count)
 
 // Inference forward pass of M rows in one fused launch (no scratch, nothing
 // kept), on `stream`.
+// The fused forward's LDS image of the current parameters and normalisation.
+sp_status mlp_stage(sp_mlp* mm, hipStream_t stream)
+{
+    if (!mm->wsw_stale) return SP_OK;
+    hipLaunchKernelGGL(stage_forward_kernel, dim3((kFwdStageThreads + 255) / 256), dim3(256), 0, stream,
+                       mm->theta_h, mm->theta, mm->norm, mm->wsw);
+    MLP_HIP(mm, hipGetLastError());
+    mm->wsw_stale = false;
+    return SP_OK;
+}
+
+// Workgroups of the fused forward over M rows.
+int64_t mlp_blocks(const sp_mlp* mm, int64_t M)
+{
+    const int64_t per_block = (int64_t)kFwdWaves * 16;
+    return std::min<int64_t>((M + per_block - 1) / per_block, 2 * (int64_t)mm->num_cus);
+}
+
 sp_status mlp_infer(sp_mlp* mm, const float* x, int64_t M, float* y, hipStream_t stream)
 {
     if (M <= 0) return SP_OK;
-    if (mm->wsw_stale) {
-        hipLaunchKernelGGL(stage_forward_kernel, dim3((kFwdStageThreads + 255) / 256), dim3(256), 0, stream,
-                           mm->theta_h, mm->theta, mm->norm, mm->wsw);
-        MLP_HIP(mm, hipGetLastError());
-        mm->wsw_stale = false;
-    }
-    const int64_t per_block = (int64_t)kFwdWaves * 16;
-    const int64_t blocks = std::min<int64_t>((M + per_block - 1) / per_block, 2 * (int64_t)mm->num_cus);
+    SP_TRY(mlp_stage(mm, stream));
+    const int64_t blocks = mlp_blocks(mm, M);
     hipLaunchKernelGGL(mlp_forward_kernel, dim3((unsigned)blocks), dim3(64 * kFwdWaves), kFwdLds, stream, x,
                        (long)M, mm->wsw, y);
     MLP_HIP(mm, hipGetLastError());

@@ -143,26 +143,115 @@ __global__ __launch_bounds__(64) void resync_kernel(const int32_t* cells, const 
     if (lane == 0 && status) status[blockIdx.x] = clamped ? RS_CLAMPED : RS_OK;
 }
 
-// Continuum step of the hybrid: closure cells Qb + dT T (Qb: the base-updated
-// state, T: the network's residual tendency, applied while the cell's reduced
-// DEM is younger than `window`, always if window <= 0), the others the LF
-// step of their statistics.
-__global__ void hybrid_continuum_kernel(CellStats st, const double* Q, const double* Qb, double* Qn,
-                                        const int32_t* row, const float* T, const double* red, double t,
-                                        double window, int nx, int ny, double dT, double dX, double dY,
-                                        double inv_area, unsigned long long* max_cfl_bits, uint32_t* err)
+// A hybrid step after the DEM cells' statistics are two launches (five before:
+// reduced statistics, base update, features, network, continuum; each was
+// latency, not bandwidth): hybrid_cells_kernel does all that is local to a cell
+// and its four neighbours, hybrid_forward_kernel the closure cells' network with
+// its inputs gathered as it loads them.  256 x 256 cells, half of them on the
+// network: 8.5 and 15.9 us a step, 36.6 before in five kernels.
+
+// One thread per cell.  The reduced DEMs of the cell and its neighbours (formed
+// again for each stencil: cheaper than a pass that stores them), the
+// base-updated state, in FP32 into Qf as the closure's inputs.  A closure cell
+// (row >= 0) keeps the base-updated state in Qn for the network to add to,
+// writes its coefficient <v> into the step's statistics, which the checks read,
+// and the rest of its inputs into tail: ocean current, curl, A_ice / A | mean h,
+// r2m, relative velocity | relative spin, whether the network acts (its reduced
+// DEM is younger than window, or window <= 0).  The others take the LF step of
+// their statistics, with reduced coefficients for closure neighbours.
+__global__ __launch_bounds__(64) void hybrid_cells_kernel(CellStats st, double* ub, double* vb, const double* Q,
+                                                          double* Qn, float4* Qf, float4* tail, const int32_t* row,
+                                                          ClosureArgs a, const float* desc, double window, double dT,
+                                                          double inv_area, unsigned long long* max_cfl_bits,
+                                                          uint32_t* err)
 {
     const int C = blockIdx.x * blockDim.x + threadIdx.x;
-    const int nc = nx * ny;
+    const int nc = a.nx * a.ny;
     if (C >= nc) return;
-    const int q = row[C];
-    if (q >= 0) {
-        const double w = (window <= 0.0 || t - red[(size_t)C * 4 + 3] < window) ? dT : 0.0;
+    const LfNeighbours b = lf_neighbours(C, a.nx, a.ny, false);
+    const size_t m = (size_t)st.stride;
+    const int rC = row[C], rE = row[b.E], rW = row[b.W], rN = row[b.N], rS = row[b.S];
+    double o[kLfOps];
+    stencil_states(b, Q, nc, o);
+    double sC[5], unused, base[4];
+    reduced_stats(C, a.red, a.mf, a.oc, a.t, sC);
+    reduced_coefficient(b.E, a, o[16], unused);
+    reduced_coefficient(b.W, a, o[17], unused);
+    reduced_coefficient(b.N, a, unused, o[18]);
+    reduced_coefficient(b.S, a, unused, o[19]);
+    base_update(sC, o[16], o[17], o[18], o[19], o, dT, a.dX, a.dY, base);
+    Qf[C] = make_float4((float)base[0], (float)base[1], (float)base[2], (float)base[3]);
+    double q[4];
+    if (rC >= 0) {
 #pragma unroll
-        for (int f = 0; f < 4; ++f) Qn[(size_t)f * nc + C] = Qb[(size_t)f * nc + C] + w * (double)T[(size_t)q * 4 + f];
+        for (int f = 0; f < 4; ++f) q[f] = base[f];
+        ub[(size_t)C * m] = sC[0];
+        vb[(size_t)C * m] = sC[1];
+        const CellOcean oc = centre_of(C, a.oc);
+        double dux, duy, dw;
+        reduced_rel(C, a.red, a.mf, a.t, dux, duy, dw);
+        const bool acts = window <= 0.0 || a.t - a.red[(size_t)C * 4 + 3] < window;
+        float4* const to = tail + (size_t)rC * 3;
+        to[0] = make_float4((float)oc.u, (float)oc.v, (float)oc.zeta, desc[(size_t)C * 6]);
+        to[1] = make_float4(desc[(size_t)C * 6 + 1], desc[(size_t)C * 6 + 2], (float)dux, (float)duy);
+        to[2] = make_float4((float)dw, acts ? 1.0f : 0.0f, 0.0f, 0.0f);
     } else {
-        lf_cell(C, st, Q, Qn, nx, ny, dT, dX, dY, inv_area, max_cfl_bits, err, false);   // the hybrid has no walls
+        if (rE < 0) o[16] = st.ub[b.E * m];
+        if (rW < 0) o[17] = st.ub[b.W * m];
+        if (rN < 0) o[18] = st.vb[b.N * m];
+        if (rS < 0) o[19] = st.vb[b.S * m];
+        o[20] = st.ub[C * m];
+        o[21] = st.vb[C * m];
+        o[22] = st.sw[C * m];
+        o[23] = st.sx[C * m];
+        o[24] = st.sy[C * m];
+        const double cfl = lf_update(o, q, dT, a.dX, a.dY, inv_area);
+        const unsigned long long bits = (unsigned long long)__double_as_longlong(cfl);
+        if (bits > *max_cfl_bits) atomicMax(max_cfl_bits, bits);
+        if (cfl > 1.0) atomicOr(err, kErrCFL);
     }
+#pragma unroll
+    for (int f = 0; f < 4; ++f) Qn[(size_t)f * nc + C] = q[f];
+}
+
+// The closure cells' new state: the base-updated one (in Qn) plus dT times the
+// network's residual tendency where it acts.  A lane's four inputs of a block
+// are one cell of the 3 x 3 neighbourhood (features 16 kb + 4 g + q: cell 4 kb +
+// g, field q) or one record of the tail.
+__global__ __launch_bounds__(64 * spmlp::kFwdWaves) __attribute__((amdgpu_waves_per_eu(4))) void hybrid_forward_kernel(
+    const int32_t* cells, long M, const unsigned char* img, const float4* Qf, const float4* tail, int nx, int ny,
+    double dT, double* Qn)
+{
+    extern __shared__ __align__(16) unsigned char hyb_smem[];
+    const int nc = nx * ny;
+    spmlp::forward_rows(
+        M, img, hyb_smem,
+        [&](long row, int g4, float(&xv)[12]) {
+            const int C = cells[row], ix = C % nx, iy = C / nx, g = g4 >> 2;
+            float4 v[3];
+#pragma unroll
+            for (int kb = 0; kb < 3; ++kb) {
+                const int nb = min(4 * kb + g, 8), dy = nb / 3 - 1, dx = nb - 3 * (dy + 1) - 1;
+                const int x = ix + dx < 0 ? nx - 1 : ix + dx == nx ? 0 : ix + dx;
+                const int y = iy + dy < 0 ? ny - 1 : iy + dy == ny ? 0 : iy + dy;
+                const float4* at = Qf + y * nx + x;
+                if (kb == 2 && g) at = tail + row * 3 + g - 1;
+                v[kb] = *at;
+            }
+#pragma unroll
+            for (int kb = 0; kb < 3; ++kb) {
+                xv[4 * kb] = v[kb].x;
+                xv[4 * kb + 1] = v[kb].y;
+                xv[4 * kb + 2] = v[kb].z;
+                xv[4 * kb + 3] = v[kb].w;
+            }
+        },
+        [&](long row, const float(&y)[spmlp::kOut]) {
+            const int C = cells[row];
+            const double w = tail[row * 3 + 2].y != 0.0f ? dT : 0.0;
+#pragma unroll
+            for (int f = 0; f < 4; ++f) Qn[(size_t)f * nc + C] = Qn[(size_t)f * nc + C] + w * (double)y[f];
+        });
 }
 
 // Plain-method residual tendency (LF(Q) - Qb) / dT of the listed cells: their
@@ -223,15 +312,14 @@ struct HybridState {
                                           // their statistics go to scratch)
     std::vector<int32_t> clos_h;          // closure-mode cells
     int32_t* clos_d = nullptr;
-    int32_t* row_d = nullptr;             // [ncells] row of a closure-mode cell in X and T, else -1
-    float* X = nullptr;                   // [nclos][45]
-    float* T = nullptr;                   // [nclos][4]
+    int32_t* row_d = nullptr;             // [ncells] row of a closure-mode cell in clos_d, else -1
+    float4* Qf = nullptr;                 // [ncells] base-updated continuum state in FP32 (closure inputs)
+    float4* tail = nullptr;               // [nclos][3] the closure cells' other inputs
     int32_t* chk_d = nullptr;             // sampled cells of a check
     float* Xk = nullptr;
     float* Tk = nullptr;
     float* Tdem = nullptr;
     double* Qs = nullptr;                 // base-updated continuum state [4][ncells]
-    double* rs = nullptr;                 // reduced DEM statistics of every cell at the step's time [ncells][5]
     int32_t* back_d = nullptr;            // cells whose fallback window ended [ncells]
     int ndem = 0;
     // the next block's DEM launch beside this block's closure work: its stream,
@@ -249,14 +337,14 @@ void hybrid_free_buffers(HybridState* h)
         if (b.work_d) (void)hipFree(b.work_d);
         b.work_d = nullptr;
     }
-    void* ps[] = {h->clos_d, h->row_d, h->X, h->T, h->chk_d, h->Xk, h->Tk, h->Tdem, h->Qs,
-                  h->back_d, h->rs};
+    void* ps[] = {h->clos_d, h->row_d, h->Qf, h->tail, h->chk_d, h->Xk, h->Tk, h->Tdem, h->Qs,
+                  h->back_d};
     for (void* p : ps)
         if (p) (void)hipFree(p);
     h->clos_d = h->row_d = h->chk_d = h->back_d = nullptr;
-    h->X = h->T = h->Xk = h->Tk = h->Tdem = nullptr;
+    h->Xk = h->Tk = h->Tdem = nullptr;
+    h->Qf = h->tail = nullptr;
     h->Qs = nullptr;
-    h->rs = nullptr;
 }
 
 // Rebuild the DEM buckets and the closure list from the current modes.
@@ -284,8 +372,7 @@ sp_status hybrid_rebuild(sp_ctx* c)
     if (!h->clos_d) {   // sized for every cell once: modes change without reallocation
         const size_t nc = (size_t)c->ncells;
         SP_TRY(dalloc(c, &h->clos_d, nc));
-        SP_TRY(dalloc(c, &h->X, nc * spmlp::kIn));
-        SP_TRY(dalloc(c, &h->T, nc * spmlp::kOut));
+        SP_TRY(dalloc(c, &h->tail, nc * 3));
     }
     if (!h->clos_h.empty())
         HIP_TRY(c, hipMemcpyAsync(h->clos_d, h->clos_h.data(), h->clos_h.size() * 4, hipMemcpyHostToDevice,
@@ -542,7 +629,9 @@ sp_status sp_hybrid_set(sp_ctx* c, sp_mlp* net, const uint8_t* closure_cells, in
     SP_TRY(dalloc(c, &h->Tk, nk * spmlp::kOut));
     SP_TRY(dalloc(c, &h->Tdem, nk * spmlp::kOut));
     SP_TRY(dalloc(c, &h->Qs, (size_t)c->ncells * 4));
-    SP_TRY(dalloc(c, &h->rs, (size_t)c->ncells * 5));
+    SP_TRY(dalloc(c, &h->Qf, (size_t)c->ncells));
+    HIP_TRY(c, hipFuncSetAttribute(reinterpret_cast<const void*>(hybrid_forward_kernel),
+                                   hipFuncAttributeMaxDynamicSharedMemorySize, (int)spmlp::kFwdLds));
     SP_TRY(dalloc(c, &h->back_d, (size_t)c->ncells));
     SP_TRY(upload_phase(c));
     SP_TRY(ensure_cell_data(c));
@@ -639,33 +728,25 @@ sp_status sp_step_hybrid(sp_ctx* c, double dt, int64_t nsteps)
             const int64_t k = c->kstep;
             const CellStats st = ring ? stats_of_slot(ring + (size_t)t * slot, c->ncells) : stats_of_rows(c->momb[k & 1]);
             const int nclos = (int)h->clos_h.size();
-            if (nclos > 0) {
-                // base-updated level-k state, the network's residual for its
-                // features, the closure cells' coefficients from their reduced DEMs
-                ClosureArgs ca = closure_args(c, c->t_now);
-                // (the closure cells' <v> go into this step's statistics as well)
-                hipLaunchKernelGGL(reduced_stats_kernel, dim3((c->ncells + 255) / 256), dim3(256), 0, c->stream, ca,
-                                   h->rs, h->row_d, const_cast<double*>(st.ub), const_cast<double*>(st.vb), st.stride);
-                HIP_TRY(c, hipGetLastError());
-                ca.rs = h->rs;   // every cell's reduced statistics once, read by the stencils below
-                hipLaunchKernelGGL(base_kernel, dim3((c->ncells + 127) / 128), dim3(128), 0, c->stream, c->Q[k & 1],
-                                   h->Qs, ca, dt);
-                HIP_TRY(c, hipGetLastError());
-                hipLaunchKernelGGL(features_kernel, dim3((nclos + 127) / 128), dim3(128), 0, c->stream, h->clos_d,
-                                   nclos, h->Qs, ca, c->desc, h->X);
-                HIP_TRY(c, hipGetLastError());
-                SP_TRY(net_forward_on(c, h->net, h->X, nclos, h->T));
-            }
             // DEM step of the other cells (statistics of level k), and of the
             // check pool's closure cells (statistics into scratch: the closure
             // drives them); in a block, already done
             if (!ring)
                 for (auto& b : h->bk) SP_TRY(launch_bucket(c, b, base, k, false));
-            hipLaunchKernelGGL(hybrid_continuum_kernel, dim3((c->ncells + 127) / 128), dim3(128), 0, c->stream, st,
-                               c->Q[k & 1], h->Qs, c->Q[(k + 1) & 1], h->row_d, h->T, c->red, c->t_now,
-                               h->net_window, c->p.nx, c->p.ny, dt, c->p.cell_lx, c->p.cell_ly, inv_area,
-                               c->cfl_bits_d, c->err_d);
+            double* const Qn = c->Q[(k + 1) & 1];
+            const ClosureArgs ca = closure_args(c, c->t_now);
+            hipLaunchKernelGGL(hybrid_cells_kernel, dim3((c->ncells + 63) / 64), dim3(64), 0, c->stream, st,
+                               const_cast<double*>(st.ub), const_cast<double*>(st.vb), c->Q[k & 1], Qn, h->Qf, h->tail,
+                               h->row_d, ca, c->desc, h->net_window, dt, inv_area, c->cfl_bits_d, c->err_d);
             HIP_TRY(c, hipGetLastError());
+            if (nclos > 0) {
+                const sp_status ns = mlp_stage(h->net, c->stream);
+                if (ns) return fail(c, ns, "closure network: %s", h->net->err.c_str());
+                hipLaunchKernelGGL(hybrid_forward_kernel, dim3((unsigned)mlp_blocks(h->net, nclos)),
+                                   dim3(64 * spmlp::kFwdWaves), spmlp::kFwdLds, c->stream, h->clos_d, (long)nclos,
+                                   h->net->wsw, h->Qf, h->tail, c->p.nx, c->p.ny, dt, Qn);
+                HIP_TRY(c, hipGetLastError());
+            }
             h->last = st;
             c->kstep++;
             c->steps++;

@@ -277,12 +277,14 @@ __global__ void stage_forward_kernel(const uint16_t* th, const float* theta, con
     reinterpret_cast<float*>(img + kFwdOffNorm)[e] = v;
 }
 
-// img: the staged image (stage_forward_kernel); x [M][45] raw inputs, y [M][4]
-// outputs in physical units.
-__global__ __launch_bounds__(64 * kFwdWaves) __attribute__((amdgpu_waves_per_eu(4))) void mlp_forward_kernel(const float* x, long M, const unsigned char* img,
-                                                                     float* y)
+// The forward over M rows by the launch's workgroups (64 kFwdWaves threads, LDS
+// for the staged image img): load(row, g4, x) gives the lane's raw inputs
+// x[4 kb + q] = feature 16 kb + g4 + q of its row (any finite value beyond the
+// last), store(row, y) takes the outputs in physical units.
+template <class Load, class Store>
+__device__ __forceinline__ void forward_rows(long M, const unsigned char* img, unsigned char* fwd_smem, Load load,
+                                             Store store)
 {
-    extern __shared__ __align__(16) unsigned char fwd_smem[];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int g4 = 4 * (lane >> 4);
     const long step = (long)gridDim.x * kFwdWaves * 16;
@@ -291,9 +293,7 @@ __global__ __launch_bounds__(64 * kFwdWaves) __attribute__((amdgpu_waves_per_eu(
     float xv[12];
     auto load_inputs = [&](long r0) {
         const long row = r0 + (lane & 15);
-        const float* xr = x + (row < M ? row : M - 1) * kIn;
-#pragma unroll
-        for (int i = 0; i < 12; ++i) xv[i] = xr[min((i >> 2) * 16 + g4 + (i & 3), kIn - 1)];
+        load(row < M ? row : M - 1, g4, xv);
     };
     long r0 = ((long)blockIdx.x * kFwdWaves + wave) * 16;
     if (r0 < M) load_inputs(r0);   // in flight with the staging
@@ -354,11 +354,32 @@ __global__ __launch_bounds__(64 * kFwdWaves) __attribute__((amdgpu_waves_per_eu(
         // lanes 0-15 hold outputs 0-3 of row lane
         if (lane < 16 && ok) {
             const float* b4 = bias + 3 * kHid;
+            float y[kOut];
 #pragma unroll
-            for (int r = 0; r < 4; ++r) y[row * kOut + r] = (acc[r] + b4[r]) * ys[r] + ym[r];
+            for (int r = 0; r < 4; ++r) y[r] = (acc[r] + b4[r]) * ys[r] + ym[r];
+            store(row, y);
         }
         if (r0 + step < M) load_inputs(r0 + step);
     }
+}
+
+// img: the staged image (stage_forward_kernel); x [M][45] raw inputs, y [M][4]
+// outputs in physical units.
+__global__ __launch_bounds__(64 * kFwdWaves) __attribute__((amdgpu_waves_per_eu(4))) void mlp_forward_kernel(
+    const float* x, long M, const unsigned char* img, float* y)
+{
+    extern __shared__ __align__(16) unsigned char fwd_smem[];
+    forward_rows(
+        M, img, fwd_smem,
+        [&](long row, int g4, float(&xv)[12]) {
+            const float* xr = x + row * kIn;
+#pragma unroll
+            for (int i = 0; i < 12; ++i) xv[i] = xr[min((i >> 2) * 16 + g4 + (i & 3), kIn - 1)];
+        },
+        [&](long row, const float(&out)[kOut]) {
+#pragma unroll
+            for (int r = 0; r < kOut; ++r) y[row * kOut + r] = out[r];
+        });
 }
 
 __global__ void to_bf16_kernel(const float* x, int n, uint16_t* out)
