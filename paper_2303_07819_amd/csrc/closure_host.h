@@ -549,8 +549,7 @@ sp_status fused_step(sp_mlp* mm, const float* X, const float* T, const int32_t* 
     ta.dT = mm->tr_dT;
     ta.bpart = mm->tr_bpart;
     ta.lpart = mm->tr_lpart;
-    hipLaunchKernelGGL(tr_rows_kernel, dim3((unsigned)(Bp / 16)), dim3(64 * kTrSplit), kTrLdsAll, mm->stream,
-                       ta);
+    hipLaunchKernelGGL(tr_rows_kernel, dim3((unsigned)(Bp / 16)), dim3(64 * kTrSplit), 0, mm->stream, ta);
     MLP_HIP(mm, hipGetLastError());
     GradArgs ga;
     memset(&ga, 0, sizeof ga);
@@ -611,9 +610,7 @@ sp_status sp_mlp_create(void* stream, sp_mlp** out)
         hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess && cus > 0)
         mm->num_cus = cus;
     if (hipFuncSetAttribute(reinterpret_cast<const void*>(mlp_forward_kernel),
-                            hipFuncAttributeMaxDynamicSharedMemorySize, (int)kFwdLds) != hipSuccess ||
-        hipFuncSetAttribute(reinterpret_cast<const void*>(tr_rows_kernel), hipFuncAttributeMaxDynamicSharedMemorySize,
-                            (int)kTrLdsAll) != hipSuccess)
+                            hipFuncAttributeMaxDynamicSharedMemorySize, (int)kFwdLds) != hipSuccess)
         st = SP_EDEVICE;
     if (!st) st = malloc_m(mm, &mm->theta, kNParams);
     if (!st) st = malloc_m(mm, &mm->theta_h, kNParams);

@@ -1,10 +1,15 @@
 // Fused training step of the closure network: two launches per Adam step.
 //
 // tr_rows_kernel: one workgroup per 16 rows of the batch, the network's
-// weights staged in LDS as MFMA operand tiles (forward tiles as in the
+// weights as an image of MFMA operand tiles (forward tiles as in the
 // inference forward, unhalved, and the transposed tiles of W2, W3 and W4 for
 // the backward products).  Each of its eight wavefronts takes one 16-unit
-// tile of every hidden layer: forward through the four layers, each layer's
+// tile of every hidden layer, whose weights no other wavefront of the workgroup
+// reads: it holds them in registers from the start, all reads in flight with the
+// rows' own.  The chain of seven layers bounds it, not the 0.1 MFLOP per row:
+// 4096 rows, one workgroup per compute unit, take 11.7 us (13.9 with the image
+// staged in LDS, two-byte stores and scattered bias partials), 300 rows 7.6
+// (9.6).  It goes forward through the four layers, each layer's
 // output tiles exchanged through LDS to form the next product's B operand;
 // the GELU derivatives of the wavefront's own tiles kept in registers; the
 // loss gradient of the mean squared error on normalised targets (every
@@ -20,7 +25,7 @@
 // (160 tiles, those of one output block of a layer on one XCD), dW = sum over
 // rows of d^T a as 16x16x32 MFMA steps over the batch, split over eight
 // wavefronts and added in a fixed order; the bias gradients from the tile
-// partials (stored column by column) in tile order; then either the gradient
+// partials in tile order; then either the gradient
 // written out, or the Adam update of the tile's parameters with the new
 // bfloat16 weights written into the other of two LDS images for the next step.
 //
@@ -33,12 +38,11 @@
 
 namespace spmlp {
 
-constexpr int kTrSplit = 8;            // wavefronts sharing one 16-row tile in tr_rows_kernel
-constexpr int kTrTiles = 8 / kTrSplit; // 16-unit tiles of each hidden layer per wavefront
-static_assert(kTrTiles * kTrSplit == 8, "the eight tiles of a hidden layer split evenly");
+constexpr int kTrSplit = 8;            // wavefronts sharing one 16-row tile in tr_rows_kernel, a 16-unit tile each
+static_assert(kTrSplit * 16 == kHid, "a tile of every hidden layer per wavefront");
 constexpr int kTrRowAlign = 256;       // padded batch: 32-row steps for each wavefront of tr_grad_kernel
 constexpr int kTrGradWaves = 8;        // wavefronts splitting the rows of one weight-gradient tile
-// LDS image of tr_rows_kernel (bytes)
+// weight image of tr_rows_kernel (bytes)
 constexpr size_t kTrOffF1 = 0;                                   // W1: 8 x 3 tiles of 16 x 16 (bf16x4 per lane)
 constexpr size_t kTrOffF2 = kTrOffF1 + (size_t)24 * 64 * 8;      // W2: 8 x 4 tiles of 16 x 32, K permuted (bf16x8)
 constexpr size_t kTrOffF3 = kTrOffF2 + (size_t)32 * 64 * 16;     // W3
@@ -49,9 +53,6 @@ constexpr size_t kTrOffB2 = kTrOffB3 + (size_t)32 * 64 * 16;     // W2^T
 constexpr size_t kTrOffBias = kTrOffB2 + (size_t)32 * 64 * 16;  // b1, b2, b3 [128], b4 [4] (FP32)
 constexpr size_t kTrOffNorm = kTrOffBias + (size_t)(3 * kHid + kOut) * 4;   // x mean, x inv std [48 each], t mean, t inv std [4 each]
 constexpr size_t kTrLds = kTrOffNorm + (size_t)104 * 4;
-constexpr size_t kTrOffX = kTrLds;                               // layer exchange: 2 x 8 tiles x 64 lanes x bf16x4
-constexpr size_t kTrLdsAll = kTrOffX + (size_t)2 * 8 * 64 * 8;
-static_assert(kTrLdsAll <= 160 * 1024, "one training workgroup per compute unit");
 static_assert(kTrOffBias % 16 == 0 && kTrOffNorm % 16 == 0, "aligned LDS reads");
 constexpr int kTrBias = 3 * kHid + kOut;   // bias partials per tile: d1, d2, d3 [128], d4 [4]
 // activation and delta regions (offsets in features; a region of F features holds F x Bp values)
@@ -164,6 +165,23 @@ __device__ __forceinline__ long tr_at(int f, long r, int Bp)
     return ((long)(f >> 4) * (Bp >> 3) + (r >> 3)) * 128 + (f & 15) * 8 + (r & 7);
 }
 
+// Store a lane's features f0 .. f0 + 3 of batch row rr (rows along the lanes):
+// the four lanes of a quad exchange theirs (two DPP steps), so that each writes
+// four rows of one feature, 8 bytes that are consecutive there.  Two-byte stores
+// of every value took four times the write requests (0.6 us of 4096 rows' 13.7).
+__device__ __forceinline__ void tr_store4(uint16_t* to, int f0, long rr, int Bp, bf16x4 h, int lane)
+{
+    const uint2 w = __builtin_bit_cast(uint2, h);
+    const bool odd = lane & 1, upper = lane & 2;
+    auto swap1 = [](uint32_t x) { return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0xb1, 0xf, 0xf, true); };
+    auto swap2 = [](uint32_t x) { return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x4e, 0xf, 0xf, true); };
+    // rows of the pair: features 0 and 2 in its even lane, 1 and 3 in its odd one
+    const uint32_t sel = odd ? 0x03020706u : 0x05040100u;
+    const uint32_t a = __builtin_amdgcn_perm(swap1(w.x), w.x, sel), b = __builtin_amdgcn_perm(swap1(w.y), w.y, sel);
+    const uint32_t got = swap2(upper ? a : b);
+    *reinterpret_cast<uint2*>(to + tr_at(f0 + (lane & 3), rr & ~3l, Bp)) = upper ? make_uint2(got, b) : make_uint2(a, got);
+}
+
 struct TrainArgs {
     const float* X;           // [*][45] inputs
     const float* T;           // [*][4] targets
@@ -172,7 +190,7 @@ struct TrainArgs {
     const unsigned char* img; // training image (kTrLds bytes)
     uint16_t* aT;             // kTrARows x Bp activations (tr_at)
     uint16_t* dT;             // kTrDRows x Bp deltas (tr_at)
-    float* bpart;             // [kTrBias][Bp / 16] column sums of the FP32 deltas, by column then tile
+    float* bpart;             // [Bp / 16][kTrBias] column sums of the FP32 deltas of every tile
     double* lpart;            // [Bp / 16] squared errors
 };
 
@@ -253,81 +271,119 @@ __device__ __forceinline__ float row16_sum(float x)
     return x;
 }
 
+// Sum over each row of 16 lanes, in every lane: partners 8, 4, 2 and 1 apart, by
+// rotations of the row (the values repeat with the distance already summed).
+// The chain of exchanges through LDS that this replaces was 30 deep in one
+// wavefront while the other seven waited for it (1 us).
+template <int N>
+__device__ __forceinline__ float row_rotate(float x)
+{
+    return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), 0x120 + N, 0xf, 0xf, true));
+}
+
+template <int N>
+__device__ __forceinline__ double row_rotate(double x)
+{
+    const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(x), 0x120 + N, 0xf, 0xf, true);
+    const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(x), 0x120 + N, 0xf, 0xf, true);
+    return __hiloint2double(hi, lo);
+}
+
+template <class T>
+__device__ __forceinline__ T row16_ring_sum(T x)
+{
+    x += row_rotate<8>(x);
+    x += row_rotate<4>(x);
+    x += row_rotate<2>(x);
+    x += row_rotate<1>(x);
+    return x;
+}
+
 // Delta tile of a hidden layer: dz = dh * GELU'(z) (zero for rows past the
 // batch), its column sums over the 16 rows into the bias partials, and the
 // bfloat16 copy stored (tr_at) and returned as the next B operand.
 __device__ __forceinline__ bf16x4 tr_delta(const f32x4 dh, const f32x4 gpz, bool ok, int lane, int f0, long rr, int Bp,
-                                          uint16_t* dT, float* bp, int bstride)
+                                          uint16_t* dT, float* bp)
 {
-    float d[4];
+    float d[4], sum[4];
 #pragma unroll
     for (int r = 0; r < 4; ++r) d[r] = ok ? dh[r] * gpz[r] : 0.0f;
 #pragma unroll
-    for (int r = 0; r < 4; ++r) {
-        const float s = row16_sum(d[r]);
-        if ((lane & 15) == 15) bp[(size_t)(f0 + r) * bstride] = s;
-    }
+    for (int r = 0; r < 4; ++r) sum[r] = row16_sum(d[r]);
+    if ((lane & 15) == 15) *reinterpret_cast<f32x4*>(bp + f0) = f32x4{sum[0], sum[1], sum[2], sum[3]};
     const bf16x4 h = to_bf16x4(d[0], d[1], d[2], d[3]);
-#pragma unroll
-    for (int r = 0; r < 4; ++r) dT[tr_at(f0 + r, rr, Bp)] = (uint16_t)h[r];
+    tr_store4(dT, f0, rr, Bp, h, lane);
     return h;
 }
 
 __global__ __launch_bounds__(64 * kTrSplit) void tr_rows_kernel(TrainArgs ta)
 {
-    extern __shared__ __align__(16) unsigned char tr_smem[];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int tile = blockIdx.x;
     const int g4 = 4 * (lane >> 4);
     const long rr = (long)tile * 16 + (lane & 15);
     const bool ok = rr < ta.B;
-    const long src = ta.rows ? (long)ta.rows[ok ? rr : ta.B - 1] : (ok ? rr : ta.B - 1);
-    // the row's raw inputs and targets (every wavefront of the tile), in flight with the staging
+    // the row's index, read unconditionally (a branch would wait for it before
+    // the weights are asked for)
+    const long at = ok ? rr : ta.B - 1;
+    const int32_t listed = *(ta.rows ? ta.rows + at : reinterpret_cast<const int32_t*>(ta.img));
+    // the wavefront's weight tiles, biases and the normalisation, and the row's
+    // raw inputs and targets (every wavefront of the tile), in the order of their
+    // use, all in flight together
+    const bf16x4* F1 = reinterpret_cast<const bf16x4*>(ta.img + kTrOffF1) + wave * 3 * 64 + lane;
+    const bf16x8* F2 = reinterpret_cast<const bf16x8*>(ta.img + kTrOffF2) + wave * 4 * 64 + lane;
+    const bf16x8* F3 = reinterpret_cast<const bf16x8*>(ta.img + kTrOffF3) + wave * 4 * 64 + lane;
+    const bf16x8* F4 = reinterpret_cast<const bf16x8*>(ta.img + kTrOffF4) + g4 + (lane & 3);
+    const bf16x4* B4 = reinterpret_cast<const bf16x4*>(ta.img + kTrOffB4) + wave * 64 + lane;
+    const bf16x8* B3 = reinterpret_cast<const bf16x8*>(ta.img + kTrOffB3) + wave * 4 * 64 + lane;
+    const bf16x8* B2 = reinterpret_cast<const bf16x8*>(ta.img + kTrOffB2) + wave * 4 * 64 + lane;
+    const float* bias = reinterpret_cast<const float*>(ta.img + kTrOffBias);
+    const float* nrm = reinterpret_cast<const float*>(ta.img + kTrOffNorm);
+    f32x4 xm[3], xs[3], bh[3];
+    bf16x4 w1[3], v4;
+    bf16x8 w2[4], w3[4], w4[4], v3[4], v2[4];
+#pragma unroll
+    for (int kb = 0; kb < 3; ++kb) {
+        xm[kb] = *reinterpret_cast<const f32x4*>(nrm + kb * 16 + g4);
+        xs[kb] = *reinterpret_cast<const f32x4*>(nrm + 48 + kb * 16 + g4);
+        bh[kb] = *reinterpret_cast<const f32x4*>(bias + kb * kHid + wave * 16 + g4);
+        w1[kb] = F1[kb * 64];
+    }
+    __builtin_amdgcn_sched_barrier(0);
+    const long src = ta.rows ? (long)listed : at;
     float xr[12], tr[4];
 #pragma unroll
     for (int i = 0; i < 12; ++i) xr[i] = ta.X[src * kIn + min((i >> 2) * 16 + g4 + (i & 3), kIn - 1)];
-
 #pragma unroll
     for (int o = 0; o < 4; ++o) tr[o] = ta.T[src * kOut + o];
-    {
-        // eight reads in flight before their writes, the image in rounds of eight
-        constexpr int kVec = (int)(kTrLds / 16), kStride = 64 * kTrSplit;
-        const uint4* srcv = reinterpret_cast<const uint4*>(ta.img);
-        uint4* dst = reinterpret_cast<uint4*>(tr_smem);
-        for (int base = 0; base < kVec; base += 8 * kStride) {
-            uint4 t[8];
+    __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-            for (int i = 0; i < 8; ++i) t[i] = srcv[min(base + tid + i * kStride, kVec - 1)];
+    for (int kb = 0; kb < 4; ++kb) w2[kb] = F2[kb * 64];
 #pragma unroll
-            for (int i = 0; i < 8; ++i) {
-                const int e = base + tid + i * kStride;
-                if (e < kVec) dst[e] = t[i];
-            }
-        }
-    }
-    __syncthreads();
-    const bf16x4* F1 = reinterpret_cast<const bf16x4*>(tr_smem + kTrOffF1);
-    const bf16x8* F2 = reinterpret_cast<const bf16x8*>(tr_smem + kTrOffF2);
-    const bf16x8* F3 = reinterpret_cast<const bf16x8*>(tr_smem + kTrOffF3);
-    const bf16x8* F4 = reinterpret_cast<const bf16x8*>(tr_smem + kTrOffF4);
-    const bf16x4* B4 = reinterpret_cast<const bf16x4*>(tr_smem + kTrOffB4);
-    const bf16x8* B3 = reinterpret_cast<const bf16x8*>(tr_smem + kTrOffB3);
-    const bf16x8* B2 = reinterpret_cast<const bf16x8*>(tr_smem + kTrOffB2);
-    const float* bias = reinterpret_cast<const float*>(tr_smem + kTrOffBias);
-    const float* nrm = reinterpret_cast<const float*>(tr_smem + kTrOffNorm);
+    for (int kb = 0; kb < 4; ++kb) w3[kb] = F3[kb * 64];
+#pragma unroll
+    for (int kb = 0; kb < 4; ++kb) w4[kb] = F4[kb * 16];
+    const f32x4 bo = *reinterpret_cast<const f32x4*>(bias + 3 * kHid);
+    const f32x4 tm = *reinterpret_cast<const f32x4*>(nrm + 96), ts = *reinterpret_cast<const f32x4*>(nrm + 100);
+    v4 = B4[0];
+#pragma unroll
+    for (int kb = 0; kb < 4; ++kb) v3[kb] = B3[kb * 64];
+#pragma unroll
+    for (int kb = 0; kb < 4; ++kb) v2[kb] = B2[kb * 64];
+    __builtin_amdgcn_sched_barrier(0);
+    __shared__ __align__(16) unsigned char exchange[2 * 8 * 64 * sizeof(bf16x4)];
     // exchange of a layer's output tiles: buffer q holds tile t of lane l as
     // the (t % 2) half of bf16x8 slot (q 4 + t / 2) 64 + l, so that one read
     // gives the next product's B operand of K block t / 2
-    bf16x4* xw = reinterpret_cast<bf16x4*>(tr_smem + kTrOffX);
-    const bf16x8* xr8 = reinterpret_cast<const bf16x8*>(tr_smem + kTrOffX);
+    bf16x4* xw = reinterpret_cast<bf16x4*>(exchange);
+    const bf16x8* xr8 = reinterpret_cast<const bf16x8*>(exchange);
     auto put = [&](int q, int t, const bf16x4 h) { xw[2 * ((q * 4 + (t >> 1)) * 64 + lane) + (t & 1)] = h; };
     auto get = [&](int q, bf16x8* b) {
 #pragma unroll
         for (int kb = 0; kb < 4; ++kb) b[kb] = xr8[(q * 4 + kb) * 64 + lane];
     };
     const int Bp = ta.Bp;
-    const int ntile = Bp >> 4;
-    float* bp = ta.bpart + tile;   // bias partial of column c at bp[c ntile]
+    float* bp = ta.bpart + (size_t)tile * kTrBias;
 
     // ---- inputs: features 4 (lane / 16) + q of each 16-feature block, normalised
     bf16x4 xb[3];
@@ -337,17 +393,14 @@ __global__ __launch_bounds__(64 * kTrSplit) void tr_rows_kernel(TrainArgs ta)
         float v[4];
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
-            v[q] = ok ? (xr[kb * 4 + q] - nrm[f0 + q]) * nrm[48 + f0 + q] : 0.0f;
+            v[q] = ok ? (xr[kb * 4 + q] - xm[kb][q]) * xs[kb][q] : 0.0f;
         }
         xb[kb] = to_bf16x4(v[0], v[1], v[2], v[3]);
-        if (kb % kTrSplit == wave) {
-#pragma unroll
-            for (int q = 0; q < 4; ++q) ta.aT[tr_at(kTrA0 + f0 + q, rr, Bp)] = (uint16_t)xb[kb][q];
-        }
+        if (kb % kTrSplit == wave) tr_store4(ta.aT, kTrA0 + f0, rr, Bp, xb[kb], lane);
     }
     // ---- forward: z = bias + W a, a' = GELU(z) in bfloat16, GELU'(z) kept in
-    // registers; this wavefront takes output tiles wave kTrTiles .. + kTrTiles - 1
-    f32x4 gz[3][kTrTiles];
+    // registers; this wavefront takes output tile `wave`
+    f32x4 gz[3];
     auto hidden = [&](const f32x4 z, int layer, int ob, bf16x4& out, f32x4& gd) {
         float a[4], d[4];
 #pragma unroll
@@ -359,43 +412,36 @@ __global__ __launch_bounds__(64 * kTrSplit) void tr_rows_kernel(TrainArgs ta)
         out = to_bf16x4(a[0], a[1], a[2], a[3]);
         gd = f32x4{d[0], d[1], d[2], d[3]};
         const int arow = (layer == 0 ? kTrA1 : layer == 1 ? kTrA2 : kTrA3) + ob * 16 + g4;
-#pragma unroll
-        for (int r = 0; r < 4; ++r) ta.aT[tr_at(arow + r, rr, Bp)] = (uint16_t)out[r];
+        tr_store4(ta.aT, arow, rr, Bp, out, lane);
     };
     bf16x8 b[4];
+    {
+        f32x4 acc = bh[0];
 #pragma unroll
-    for (int j = 0; j < kTrTiles; ++j) {
-        const int ob = wave * kTrTiles + j;
-        f32x4 acc = *reinterpret_cast<const f32x4*>(bias + ob * 16 + g4);
-#pragma unroll
-        for (int kb = 0; kb < 3; ++kb) acc = mfma_step(F1[(ob * 3 + kb) * 64 + lane], xb[kb], acc);
+        for (int kb = 0; kb < 3; ++kb) acc = mfma_step(w1[kb], xb[kb], acc);
         bf16x4 h;
-        hidden(acc, 0, ob, h, gz[0][j]);
-        put(0, ob, h);
+        hidden(acc, 0, wave, h, gz[0]);
+        put(0, wave, h);
     }
     __syncthreads();
     get(0, b);
+    {
+        f32x4 acc = bh[1];
 #pragma unroll
-    for (int j = 0; j < kTrTiles; ++j) {
-        const int ob = wave * kTrTiles + j;
-        f32x4 acc = *reinterpret_cast<const f32x4*>(bias + kHid + ob * 16 + g4);
-#pragma unroll
-        for (int kb = 0; kb < 4; ++kb) acc = mfma_step(F2[(ob * 4 + kb) * 64 + lane], b[kb], acc);
+        for (int kb = 0; kb < 4; ++kb) acc = mfma_step(w2[kb], b[kb], acc);
         bf16x4 h;
-        hidden(acc, 1, ob, h, gz[1][j]);
-        put(1, ob, h);
+        hidden(acc, 1, wave, h, gz[1]);
+        put(1, wave, h);
     }
     __syncthreads();
     get(1, b);
+    {
+        f32x4 acc = bh[2];
 #pragma unroll
-    for (int j = 0; j < kTrTiles; ++j) {
-        const int ob = wave * kTrTiles + j;
-        f32x4 acc = *reinterpret_cast<const f32x4*>(bias + 2 * kHid + ob * 16 + g4);
-#pragma unroll
-        for (int kb = 0; kb < 4; ++kb) acc = mfma_step(F3[(ob * 4 + kb) * 64 + lane], b[kb], acc);
+        for (int kb = 0; kb < 4; ++kb) acc = mfma_step(w3[kb], b[kb], acc);
         bf16x4 h;
-        hidden(acc, 2, ob, h, gz[2][j]);
-        put(0, ob, h);
+        hidden(acc, 2, wave, h, gz[2]);
+        put(0, wave, h);
     }
     __syncthreads();
     get(0, b);
@@ -405,74 +451,59 @@ __global__ __launch_bounds__(64 * kTrSplit) void tr_rows_kernel(TrainArgs ta)
     bf16x4 dy = bf16x4{0, 0, 0, 0};
     {
         f32x4 acc = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
-        const int ai = g4 + (lane & 3);
 #pragma unroll
-        for (int kb = 0; kb < 4; ++kb) acc = mfma_step(F4[kb * 16 + ai], b[kb], acc);
+        for (int kb = 0; kb < 4; ++kb) acc = mfma_step(w4[kb], b[kb], acc);
         const bool out_lane = lane < 16 && ok;
         float d[4];
         double sq = 0.0;
 #pragma unroll
         for (int o = 0; o < 4; ++o) {
-            const float y = acc[o] + bias[3 * kHid + o];
-            const float tn = (tr[o] - nrm[96 + o]) * nrm[100 + o];
+            const float y = acc[o] + bo[o];
+            const float tn = (tr[o] - tm[o]) * ts[o];
             const float e = y - tn;
             d[o] = out_lane ? 2.0f * e / (float)(ta.B * kOut) : 0.0f;
             sq += out_lane ? (double)(e * e) : 0.0;
         }
         if (lane < 16) dy = to_bf16x4(d[0], d[1], d[2], d[3]);
-        if (wave == 0) {
-#pragma unroll
-            for (int off = 32; off >= 1; off >>= 1) sq += __shfl_xor(sq, off, 64);
+        if (wave == 0) {   // sums over the 16 rows, of which lane 0 holds the total
+            sq = row16_ring_sum(sq);
             if (lane == 0) ta.lpart[tile] = sq;
+            f32x4 sum;
 #pragma unroll
-            for (int o = 0; o < 4; ++o) {
-                float s = d[o];
-#pragma unroll
-                for (int off = 32; off >= 1; off >>= 1) s += __shfl_xor(s, off, 64);
-                if (lane == 0) bp[(size_t)(3 * kHid + o) * ntile] = s;
-            }
-            if (lane < 16) {
-#pragma unroll
-                for (int o = 0; o < 4; ++o) ta.dT[tr_at(kTrD4 + o, rr, Bp)] = (uint16_t)dy[o];
-            }
+            for (int o = 0; o < 4; ++o) sum[o] = row16_ring_sum(d[o]);
+            if (lane == 0) *reinterpret_cast<f32x4*>(bp + 3 * kHid) = sum;
+            if (lane < 16) tr_store4(ta.dT, kTrD4, rr, Bp, dy, lane);
         }
     }
     // ---- backward: dh3 = W4^T dy, then W3^T d3 and W2^T d2, this wavefront's
-    // tiles of each, exchanged like the forward's
-#pragma unroll
-    for (int j = 0; j < kTrTiles; ++j) {
-        const int ib = wave * kTrTiles + j;
-        const f32x4 dh = mfma_step(B4[ib * 64 + lane], dy, f32x4{0.0f, 0.0f, 0.0f, 0.0f});
-        put(1, ib, tr_delta(dh, gz[2][j], ok, lane, ib * 16 + g4, rr, Bp, ta.dT + (long)kTrD3 * Bp,
-                                     bp + (size_t)2 * kHid * ntile, ntile));
+    // tile of each, exchanged like the forward's
+    const int f0 = wave * 16 + g4;
+    {
+        const f32x4 dh = mfma_step(v4, dy, f32x4{0.0f, 0.0f, 0.0f, 0.0f});
+        put(1, wave, tr_delta(dh, gz[2], ok, lane, f0, rr, Bp, ta.dT + (long)kTrD3 * Bp, bp + 2 * kHid));
     }
     __syncthreads();
     get(1, b);
-#pragma unroll
-    for (int j = 0; j < kTrTiles; ++j) {
-        const int ib = wave * kTrTiles + j;
+    {
         f32x4 acc = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
 #pragma unroll
-        for (int kb = 0; kb < 4; ++kb) acc = mfma_step(B3[(ib * 4 + kb) * 64 + lane], b[kb], acc);
-        put(0, ib, tr_delta(acc, gz[1][j], ok, lane, ib * 16 + g4, rr, Bp, ta.dT + (long)kTrD2 * Bp,
-                                     bp + (size_t)kHid * ntile, ntile));
+        for (int kb = 0; kb < 4; ++kb) acc = mfma_step(v3[kb], b[kb], acc);
+        put(0, wave, tr_delta(acc, gz[1], ok, lane, f0, rr, Bp, ta.dT + (long)kTrD2 * Bp, bp + kHid));
     }
     __syncthreads();
     get(0, b);
-#pragma unroll
-    for (int j = 0; j < kTrTiles; ++j) {
-        const int ib = wave * kTrTiles + j;
+    {
         f32x4 acc = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
 #pragma unroll
-        for (int kb = 0; kb < 4; ++kb) acc = mfma_step(B2[(ib * 4 + kb) * 64 + lane], b[kb], acc);
-        (void)tr_delta(acc, gz[0][j], ok, lane, ib * 16 + g4, rr, Bp, ta.dT + (long)kTrD1 * Bp, bp, ntile);
+        for (int kb = 0; kb < 4; ++kb) acc = mfma_step(v2[kb], b[kb], acc);
+        (void)tr_delta(acc, gz[0], ok, lane, f0, rr, Bp, ta.dT + (long)kTrD1 * Bp, bp);
     }
 }
 
 struct GradArgs {
     const uint16_t* aT;       // [kTrARows][Bp]
     const uint16_t* dT;       // [kTrDRows][Bp]
-    const float* bpart;       // [kTrBias][ntile]
+    const float* bpart;       // [ntile][kTrBias]
     const double* lpart;      // [ntile]
     int ntile, Bp;
     float* grad;              // gradient mode: [kNParams] out
@@ -491,8 +522,10 @@ struct GradArgs {
 // th0 read before; returns the new value.
 __device__ __forceinline__ float tr_adam(const GradArgs& g, int idx, float gi, float m0, float v0, float th0)
 {
-    const float mi = g.b1 * m0 + (1.0f - g.b1) * gi;
-    const float vi = g.b2 * v0 + (1.0f - g.b2) * gi * gi;
+    // the fused products written out: a rounding of the moments that depended on
+    // the code around them would reach the bfloat16 weights
+    const float mi = fmaf(1.0f - g.b1, gi, g.b1 * m0);
+    const float vi = fmaf(gi, (1.0f - g.b2) * gi, g.b2 * v0);
     g.m[idx] = mi;
     g.v[idx] = vi;
     const float mh = mi / g.c1, vh = vi / g.c2;
@@ -547,30 +580,23 @@ __global__ __launch_bounds__(64 * kTrGradWaves) void tr_grad_kernel(GradArgs g)
         }
     }
     __shared__ float bsum[16][33];
-    const int bf = tid >> 5, bj = tid & 31;         // 32 threads per output of the tile
+    const int bf = tid & 15, bj = tid >> 4;         // 32 threads per output of the tile
     const int bo = ot * 16 + bf;
     const int boff = layer * kHid + bo;             // partial column (b4 after the three hidden layers)
-    if (it == 0) {
-        float sb = 0.0f;
-        if (bf < 16 && bo < nout)
-            for (int q0 = bj; q0 < g.ntile; q0 += 32 * 8) {   // eight reads in flight, added in tile order
-                float pv[8];
+    // (the first of each thread's partials now, with the products' operands in
+    // flight behind them; added after the products)
+    const bool bias_thread = it == 0 && bo < nout;
+    float pv[8];
+    auto partials = [&](int q0) {   // eight reads in flight, added in tile order
 #pragma unroll
-                for (int u = 0; u < 8; ++u) {
-                    const int q = q0 + 32 * u;
-                    pv[u] = q < g.ntile ? g.bpart[(size_t)boff * g.ntile + q] : 0.0f;
-                }
-#pragma unroll
-                for (int u = 0; u < 8; ++u) sb += pv[u];
-            }
-        if (bf < 16) bsum[bf][bj] = sb;
-    }
+        for (int u = 0; u < 8; ++u) {
+            const int q = q0 + 32 * u;
+            pv[u] = bias_thread && q < g.ntile ? g.bpart[(size_t)q * kTrBias + boff] : 0.0f;
+        }
+    };
+    partials(bj);
     __shared__ double lsum[64 * kTrGradWaves];
-    if (t == 0) {
-        double sl = 0.0;
-        for (int q = tid; q < g.ntile; q += 64 * kTrGradWaves) sl += g.lpart[q];
-        lsum[tid] = sl;
-    }
+    double sl = t == 0 && tid < g.ntile ? g.lpart[tid] : 0.0;
     // ---- dW tile: A = d^T (16 outputs x rows), B = a (rows x 16 inputs); rows split over the waves
     const int Bp = g.Bp, per = Bp / kTrGradWaves;
     const bf16x8* Ap = reinterpret_cast<const bf16x8*>(g.dT + tr_at(drow + ot * 16, 0, Bp));   // tile start
@@ -591,6 +617,21 @@ __global__ __launch_bounds__(64 * kTrGradWaves) void tr_grad_kernel(GradArgs g)
         for (int q = 0; q < 16; ++q) acc = mfma_step(a[q], b[q], acc);
     }
     red[wave][lane] = acc;
+    if (it == 0) {
+        float sb = 0.0f;
+#pragma unroll
+        for (int u = 0; u < 8; ++u) sb += pv[u];
+        for (int q0 = bj + 32 * 8; q0 < g.ntile; q0 += 32 * 8) {
+            partials(q0);
+#pragma unroll
+            for (int u = 0; u < 8; ++u) sb += pv[u];
+        }
+        bsum[bf][bj] = sb;
+    }
+    if (t == 0) {
+        for (int q = tid + 64 * kTrGradWaves; q < g.ntile; q += 64 * kTrGradWaves) sl += g.lpart[q];
+        lsum[tid] = sl;
+    }
     __syncthreads();
     if (wave == 0) {
         f32x4 s = red[0][lane];
@@ -616,10 +657,10 @@ __global__ __launch_bounds__(64 * kTrGradWaves) void tr_grad_kernel(GradArgs g)
     // ---- bias gradients: a fixed tree over the 32 sums of each output
     if (it == 0) {
         for (int w = 16; w >= 1; w >>= 1) {
-            if (bf < 16 && bj < w) bsum[bf][bj] += bsum[bf][bj + w];
+            if (bj < w) bsum[bf][bj] += bsum[bf][bj + w];
             __syncthreads();
         }
-        if (bf < 16 && bj == 0 && bo < nout) {
+        if (bj == 0 && bo < nout) {
             const int idx = offB + bo;
             if (!adam) {
                 g.grad[idx] = bsum[bf][0];
