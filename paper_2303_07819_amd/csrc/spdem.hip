@@ -1540,19 +1540,20 @@ sp_status sp_read_moments(sp_ctx* c, int32_t which, double* out)
     const int nc = c->ncells;
     if (which == SP_MOMENTS_DEM) {
         StepArgs a = make_args(c, 0.0);
+        const size_t bytes = (size_t)nc * SP_NMOM * sizeof(double);
+        if (nc > 0 && c->staging.reserve(bytes + sizeof(uint32_t))) {
+            uint32_t* const e = reinterpret_cast<uint32_t*>(c->staging.host + bytes);
+            hipLaunchKernelGGL(stats_read_kernel, dim3(nc), dim3(256), 0, c->stream, a,
+                               reinterpret_cast<double*>(c->staging.host), e);
+            HIP_TRY(c, hipGetLastError());
+            HIP_TRY(c, hipStreamSynchronize(c->stream));
+            memcpy(out, c->staging.host, bytes);
+            return device_err(c, *e);
+        }
         a.mom = c->mom2;
         if (nc > 0) {
             hipLaunchKernelGGL(stats_kernel, dim3(nc), dim3(256), 0, c->stream, a, nullptr, 0);
             HIP_TRY(c, hipGetLastError());
-        }
-        uint32_t e = 0;
-        hipError_t he;
-        Readout rd;
-        rd.add(out, c->mom2, (size_t)nc * SP_NMOM, true, SP_NMOM, kMomStride, 1);
-        rd.add(&e, c->err_d, 1, false);
-        if (rd.run(c->staging, c->stream, he)) {
-            HIP_TRY(c, he);
-            return device_err(c, e);
         }
         std::vector<double> buf((size_t)nc * kMomStride);
         HIP_TRY(c, hipMemcpyAsync(buf.data(), c->mom2, buf.size() * 8, hipMemcpyDeviceToHost, c->stream));
