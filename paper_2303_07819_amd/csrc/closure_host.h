@@ -300,11 +300,7 @@ __global__ __launch_bounds__(kFeatThreads) void features_kernel(const int32_t* c
                                                                 ClosureArgs a, const float* desc, float* x)
 {
     __shared__ float tile[kFeatRows * spmlp::kIn];
-    // rows by XCD (workgroups are dealt to the eight in turn): the two halves of
-    // the 128 rows that workgroup j of the network reads are written on XCD j % 8
-    int tile64 = blockIdx.x;
-    if (tile64 < (int)gridDim.x / 16 * 16) tile64 = (tile64 / 16 * 8 + tile64 % 8) * 2 + (tile64 / 8) % 2;
-    const int i0 = tile64 * kFeatRows;
+    const int i0 = blockIdx.x * kFeatRows;
     const int l = threadIdx.x % kFeatRows, p = threadIdx.x / kFeatRows;
     if (i0 + l < ncl) feature_part(cells ? cells[i0 + l] : i0 + l, p, Q, a, desc, tile + l * spmlp::kIn);
     __syncthreads();
