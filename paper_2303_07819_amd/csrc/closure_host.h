@@ -249,52 +249,67 @@ __global__ void reduced_init_kernel(const int32_t* cells, int ncl, const int32_t
     q[3] = a.t;
 }
 
-// The 45 closure inputs of cell C into o: the continuum state Q (rho, P_x, P_y,
-// P_w) on the 3 x 3 neighbourhood (row by row from the south-west, periodic),
-// the ocean current and curl at the cell centre, A_ice / A, mean h, r2m, and
-// the reduced DEM's relative velocity and spin at time t.
-__device__ __forceinline__ void cell_features(int c, const double* Q, const ClosureArgs& a, const float* desc,
-                                              float* o)
+// The 45 closure inputs of a cell in twelve parts of four: part p < 9 the
+// continuum state Q (rho, P_x, P_y, P_w) of cell p of the 3 x 3 neighbourhood
+// (row by row from the south-west, periodic), then the ocean current and curl at
+// the cell centre and A_ice / A, then mean h, r2m and the reduced DEM's relative
+// velocity at time t, then its relative spin alone.
+__device__ __forceinline__ void feature_part(int c, int p, const double* Q, const ClosureArgs& a, const float* desc,
+                                             float* o)
 {
     const int nx = a.nx, ny = a.ny, nc = nx * ny;
-    const int ix = c % nx, iy = c / nx;
-    int k = 0;
-    for (int dy = -1; dy <= 1; ++dy) {
-        const int yy = (iy + dy + ny) % ny;
-        for (int dx = -1; dx <= 1; ++dx) {
-            const int nb = yy * nx + (ix + dx + nx) % nx;
+    o += 4 * p;
+    if (p < 9) {
+        const int ix = c % nx + p % 3 - 1, iy = c / nx + p / 3 - 1;
+        const int nb = (iy < 0 ? ny - 1 : iy == ny ? 0 : iy) * nx + (ix < 0 ? nx - 1 : ix == nx ? 0 : ix);
+        double q[4];
 #pragma unroll
-            for (int f = 0; f < 4; ++f) o[k++] = (float)Q[(size_t)f * nc + nb];
+        for (int f = 0; f < 4; ++f) q[f] = Q[(size_t)f * nc + nb];
+#pragma unroll
+        for (int f = 0; f < 4; ++f) o[f] = (float)q[f];
+    } else if (p == 9) {
+        const CellOcean oc = centre_of(c, a.oc);
+        o[0] = (float)oc.u;
+        o[1] = (float)oc.v;
+        o[2] = (float)oc.zeta;
+        o[3] = desc[(size_t)c * 6 + 0];
+    } else {
+        double dux, duy, dw;
+        reduced_rel(c, a.red, a.mf, a.t, dux, duy, dw);
+        if (p == 10) {
+            o[0] = desc[(size_t)c * 6 + 1];
+            o[1] = desc[(size_t)c * 6 + 2];
+            o[2] = (float)dux;
+            o[3] = (float)duy;
+        } else {
+            o[0] = (float)dw;
         }
     }
-    const CellOcean oc = centre_of(c, a.oc);
-    o[36] = (float)oc.u;
-    o[37] = (float)oc.v;
-    o[38] = (float)oc.zeta;
-    o[39] = desc[(size_t)c * 6 + 0];
-    o[40] = desc[(size_t)c * 6 + 1];
-    o[41] = desc[(size_t)c * 6 + 2];
-    double dux, duy, dw;
-    reduced_rel(c, a.red, a.mf, a.t, dux, duy, dw);
-    o[42] = (float)dux;
-    o[43] = (float)duy;
-    o[44] = (float)dw;
 }
 
 // Features of every cell (cells == null) or of the listed cells into
-// consecutive rows of x.
-// One row per thread (blocks of at most 128 threads): the rows are built in
-// LDS and the block's contiguous span of x is written coalesced.
-__global__ __launch_bounds__(128) void features_kernel(const int32_t* cells, int ncl, const double* Q, ClosureArgs a,
-                                                       const float* desc, float* x)
+// consecutive rows of x: 128 rows per workgroup, as many as a workgroup of the
+// network reads (the same XCD then holds them), four threads per row, the rows
+// built in LDS and the workgroup's contiguous span of x written coalesced.
+// Gather and network of 256 x 256 cells, us a pass: one thread per row 15.7, two
+// 15.8, four 15.5, six 16.4; twelve on 64 rows 16.9 (12 MB written and read).
+constexpr int kFeatRows = 128, kFeatSplit = 4, kFeatThreads = kFeatSplit * kFeatRows;
+
+__global__ __launch_bounds__(kFeatThreads) void features_kernel(const int32_t* cells, int ncl, const double* Q,
+                                                                ClosureArgs a, const float* desc, float* x)
 {
-    __shared__ float tile[128 * spmlp::kIn];
-    const int i0 = blockIdx.x * blockDim.x;
-    const int i = i0 + threadIdx.x;
-    if (i < ncl) cell_features(cells ? cells[i] : i, Q, a, desc, tile + threadIdx.x * spmlp::kIn);
+    __shared__ float tile[kFeatRows * spmlp::kIn];
+    const int i0 = blockIdx.x * kFeatRows;
+    const int l = threadIdx.x % kFeatRows, p0 = threadIdx.x / kFeatRows;
+    if (i0 + l < ncl) {
+        const int c = cells ? cells[i0 + l] : i0 + l;
+#pragma unroll
+        for (int p = 0; p < 12 / kFeatSplit; ++p)
+            feature_part(c, p0 + p * kFeatSplit, Q, a, desc, tile + l * spmlp::kIn);
+    }
     __syncthreads();
-    const int rows = min((int)blockDim.x, ncl - i0);
-    for (int e = threadIdx.x; e < rows * spmlp::kIn; e += blockDim.x) x[(size_t)i0 * spmlp::kIn + e] = tile[e];
+    const int n = min(kFeatRows, ncl - i0) * spmlp::kIn;
+    for (int e = threadIdx.x; e < n; e += kFeatThreads) x[(size_t)i0 * spmlp::kIn + e] = tile[e];
 }
 
 // (Q_now - Q_ref) / dt per cell, [nc][4] FP32.
@@ -899,7 +914,7 @@ sp_status sp_closure_features(sp_ctx* c, float* x)
     SP_TRY(flush_lf(c));
     SP_TRY(upload_phase(c));
     SP_TRY(ensure_cell_data(c));
-    hipLaunchKernelGGL(features_kernel, dim3((c->ncells + 127) / 128), dim3(128), 0, c->stream, nullptr, c->ncells,
+    hipLaunchKernelGGL(features_kernel, dim3((c->ncells + kFeatRows - 1) / kFeatRows), dim3(kFeatThreads), 0, c->stream, nullptr, c->ncells,
                        c->Q[c->kstep & 1], closure_args(c, c->t_now), c->desc, x);
     HIP_TRY(c, hipGetLastError());
     return SP_OK;
@@ -927,7 +942,7 @@ sp_status sp_closure_sample(sp_ctx* c, double dt, int32_t mode, float* x, float*
     } else {
         HIP_TRY(c, hipMemcpyAsync(c->qprev, Q, (size_t)c->ncells * 4 * 8, hipMemcpyDeviceToDevice, c->stream));
     }
-    hipLaunchKernelGGL(features_kernel, dim3((c->ncells + 127) / 128), dim3(128), 0, c->stream, nullptr, c->ncells,
+    hipLaunchKernelGGL(features_kernel, dim3((c->ncells + kFeatRows - 1) / kFeatRows), dim3(kFeatThreads), 0, c->stream, nullptr, c->ncells,
                        c->qprev, a, c->desc, x);
     HIP_TRY(c, hipGetLastError());
     SP_TRY(sp_step(c, dt, 1));

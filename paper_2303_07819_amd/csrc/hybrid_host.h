@@ -464,7 +464,7 @@ sp_status hybrid_check(sp_ctx* c, double dt)
                        dt, c->p.cell_lx, c->p.cell_ly, inv_area, h->Tdem);
     HIP_TRY(c, hipGetLastError());
     // 3. the closure's residual for the same cells
-    hipLaunchKernelGGL(features_kernel, dim3((nk + 63) / 64), dim3(64), 0, c->stream, h->chk_d, nk, h->Qs, ca,
+    hipLaunchKernelGGL(features_kernel, dim3((nk + kFeatRows - 1) / kFeatRows), dim3(kFeatThreads), 0, c->stream, h->chk_d, nk, h->Qs, ca,
                        c->desc, h->Xk);
     HIP_TRY(c, hipGetLastError());
     SP_TRY(net_forward_on(c, h->net, h->Xk, nk, h->Tk));
