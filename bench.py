@@ -257,7 +257,7 @@ def main():
     ap.add_argument("--schedule", type=int, default=0)
     ap.add_argument("--step-block", type=int, default=0,
                     help="steps per DEM launch of the headline run (0: the library's default of 32; "
-                         "1: one launch per step, replayed as captured graphs)")
+                         "1: one launch per step)")
     ap.add_argument("--no-cpu-baseline", action="store_true")
     ap.add_argument("--profile-steps", type=int, default=64)
     ap.add_argument("--no-hybrid", action="store_true",

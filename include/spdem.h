@@ -332,7 +332,7 @@ sp_status sp_get_block_waves(sp_ctx* ctx, int32_t* waves);
  * (the cell DEMs never read the continuum at this cadence), each step's
  * statistics going to a k-slot ring, followed by the k continuum updates;
  * a call's remaining steps (fewer than k) run as one block of their own
- * length, so every step of sp_step is blocked and none captures a graph.  Blocked launches hold one floe per lane,
+ * length, so every step of sp_step is blocked.  Blocked launches hold one floe per lane,
  * a cell of n floes in ceil(n / 64) wavefronts (a bucket's launches group its
  * cells by that number).  Applies to sp_step with N0 = 1 (the coupled cadence
  * blocks its stretches between
@@ -352,8 +352,9 @@ sp_status sp_get_step_block(sp_ctx* ctx, int32_t* k, int32_t* active);
  * NULL).  Synchronises. */
 sp_status sp_get_work(sp_ctx* ctx, int64_t* candidate_tests, int64_t* blocked_steps);
 
-/* sp_step replays runs of `chunk` steps as one captured HIP graph (default 16;
- * 0 disables capture; must be even).  Results are identical either way. */
+/* Accepted for programs that call it, without effect: no launch is captured as
+ * a HIP graph; where blocked steps do not apply, sp_step launches step by step.
+ * Errors: SP_EINVAL (chunk negative or odd). */
 sp_status sp_set_graph_chunk(sp_ctx* ctx, int32_t chunk);
 
 /* ------------------------------------------------------------------------

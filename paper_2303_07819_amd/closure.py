@@ -265,7 +265,7 @@ def hybrid_experiment(w, net, nsteps: int, stream, marks=(10, 100, 400), window_
            "floes_in_dem_cells": int(w.counts[dem].sum()), "net_window_steps": window_steps}
     window = window_steps * w.dt
     zero = zero_network(stream.cuda_stream)
-    # warm-up: kernels loaded, graph captured, network workspace sized
+    # warm-up: kernels loaded, network workspace sized
     _evolve(w, stream, 20, (20,))
     _evolve(w, stream, 20, (20,), net, dem, window)
     full = _evolve(w, stream, nsteps, (), timed=True)

@@ -261,7 +261,6 @@ sp_status sp_set_coupling(sp_ctx* c, int32_t N0, int32_t N1, int32_t n_t)
     if (N0 > 1 && (c->p.flags & SP_NO_CONTINUUM)) return fail(c, SP_ESTATE, "coupling needs the continuum update");
     if (N0 > 1 && c->hyb) return fail(c, SP_ESTATE, "the hybrid step runs with N0 = 1");
     SP_TRY(flush_lf(c));
-    drop_graph(c);
     const bool was = c->N0 > 1;
     if (c->have_floes && c->ncells > 0) {
         // the current coarse state into both buffers (the coupled invariant;

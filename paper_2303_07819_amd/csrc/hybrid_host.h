@@ -642,7 +642,6 @@ sp_status sp_hybrid_set(sp_ctx* c, sp_mlp* net, const uint8_t* closure_cells, in
         h->red_t0.resize(c->ncells);
         for (int i = 0; i < c->ncells; ++i) h->red_t0[i] = red[(size_t)i * 4 + 3];
     }
-    drop_graph(c);
     return hybrid_rebuild(c);
 }
 

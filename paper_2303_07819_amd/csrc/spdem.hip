@@ -13,8 +13,7 @@
 // grid order or by persistent workgroups that pull cells from a counter.  W and
 // the persistent flag per bucket come from defaults or from sp_autotune, which
 // times every variant on a scratch copy of the state.  The continuum update of
-// step k runs inside the DEM launch of step k + 1, and chunks of steady-state
-// steps are replayed as one captured HIP graph.
+// step k runs inside the DEM launch of step k + 1.
 #include <hip/hip_runtime.h>
 
 #include <math.h>
@@ -45,7 +44,6 @@ constexpr int kNumBuckets = 5;
 constexpr double kSkinFrac = 0.3;   // smallest candidate-list skin, in units of the largest radius
 constexpr int kBucketHi[kNumBuckets] = {64, 128, 256, 512, SP_MAX_CELL_FLOES};
 constexpr int kDefaultWaves[kNumBuckets] = {1, 2, 4, 4, 8};
-constexpr int kDefaultGraphChunk = 16;
 constexpr int kDefaultStepBlock = 32;   // steps per blocked DEM launch
 
 // A run of a bucket's cells that one blocked launch takes: the wavefronts that
@@ -160,13 +158,6 @@ struct sp_ctx {
     bool lf_used[2] = {false, false};       // lf_done[i] was recorded
     int lf_last = -1;                       // ring half whose updates were enqueued last, not yet joined
     int64_t blk_steps = 0;                  // steps taken in blocks since the floes were set
-
-    // graph replay
-    int graph_chunk = kDefaultGraphChunk;
-    bool graph_ok = true;
-    hipGraph_t graph = nullptr;
-    hipGraphExec_t gexec = nullptr;
-    double graph_dt = 0.0;
 };
 
 // Scratch of sp_read_moments_noalloc: the statistics rows of up to
@@ -268,17 +259,8 @@ sp_status dalloc(sp_ctx* ctx, T** p, size_t count)
     return SP_OK;
 }
 
-void drop_graph(sp_ctx* c)
-{
-    if (c->gexec) (void)hipGraphExecDestroy(c->gexec);
-    if (c->graph) (void)hipGraphDestroy(c->graph);
-    c->gexec = nullptr;
-    c->graph = nullptr;
-}
-
 void free_all(sp_ctx* c)
 {
-    drop_graph(c);
     hybrid_free(c);
     coupling_free(c);
     void* ps[] = {c->xi, c->yi, c->u, c->v, c->w, c->th, c->r, c->h, c->cell_start, c->phase, c->modec, c->ocen,
@@ -429,7 +411,6 @@ sp_status upload_phase(sp_ctx* c)
     SP_TRY(upload_ocean_centres(c));
     HIP_TRY(c, hipStreamSynchronize(c->stream));
     c->phase_dirty = false;
-    drop_graph(c);
     return SP_OK;
 }
 
@@ -1037,55 +1018,6 @@ sp_status reset_continuum(sp_ctx* c)
     return SP_OK;
 }
 
-// Capture `graph_chunk` steady-state steps (entry: kstep even, continuum
-// pending unless disabled) as one graph.
-sp_status capture_graph(sp_ctx* c, double dt)
-{
-    drop_graph(c);
-    const StepArgs base = make_args(c, dt);
-    const bool cont = !(c->p.flags & SP_NO_CONTINUUM);
-    if (hipStreamBeginCapture(c->stream, hipStreamCaptureModeThreadLocal) != hipSuccess) {
-        (void)hipGetLastError();
-        c->graph_ok = false;
-        return SP_OK;
-    }
-    sp_status st = SP_OK;
-    for (int i = 0; i < c->graph_chunk && !st; ++i) {
-        for (auto& b : c->bk) {
-            st = launch_bucket(c, b, base, i, cont);
-            if (st) break;
-        }
-        if (!st && cont) st = launch_empty_lf(c, base, i);
-    }
-    hipGraph_t g = nullptr;
-    hipError_t e = hipStreamEndCapture(c->stream, &g);
-    if (st) {
-        // a launch the graph cannot hold (e.g. a workgroup above the graph's LDS
-        // limit): keep stepping eagerly
-        if (g) (void)hipGraphDestroy(g);
-        (void)hipGetLastError();
-        c->graph_ok = false;
-        c->err.clear();
-        return SP_OK;
-    }
-    if (e != hipSuccess || !g) {
-        (void)hipGetLastError();
-        c->graph_ok = false;
-        return SP_OK;
-    }
-    e = hipGraphInstantiate(&c->gexec, g, nullptr, nullptr, 0);
-    if (e != hipSuccess) {
-        (void)hipGraphDestroy(g);
-        (void)hipGetLastError();
-        c->gexec = nullptr;
-        c->graph_ok = false;
-        return SP_OK;
-    }
-    c->graph = g;
-    c->graph_dt = dt;
-    return SP_OK;
-}
-
 // Autotuning of blocked steps on a scratch copy of the state (`a` points at
 // it): the block length over the whole step (16, 32, 64 steps; the wavefronts
 // of a cell follow from its floes), each one warm-up launch and the minimum of
@@ -1247,7 +1179,6 @@ sp_status sp_set_ocean(sp_ctx* c, double u0, double v0, int32_t nmodes, const do
         c->ph[m] = phase[m];
     }
     c->phase_dirty = true;
-    drop_graph(c);
     SP_TRY(upload_phase(c));
     if (c->have_floes) {
         // the reduced DEM is relative to the current: take it again from the floes
@@ -1314,7 +1245,6 @@ static sp_status set_floes_common(sp_ctx* c, int64_t n, const int32_t* counts, c
         if (n > 0 && !src[k] && k != 4 && k != 5) return fail(c, SP_EINVAL, "null floe array %d", k);
 
     HIP_TRY(c, hipStreamSynchronize(c->stream));
-    drop_graph(c);
     hybrid_free(c);   // its cell lists follow the floes
     coupling_free(c);   // so do the coupled cadence's
     c->cpl_nudges = 0;
@@ -1429,14 +1359,13 @@ sp_status sp_step(sp_ctx* c, double dt, int64_t nsteps)
         return fail(c, SP_EINVAL, "dt must be positive and nsteps non-negative");
     SP_TRY(upload_phase(c));
     if (c->lf_pending && c->lf_dt != dt) SP_TRY(flush_lf(c));   // pending update of another dt
-    const bool cont = !(c->p.flags & SP_NO_CONTINUUM);
     const StepArgs base = make_args(c, dt);
     c->t_now += dt * (double)nsteps;
     if (c->N0 > 1) return coupled_steps(c, base, nsteps);
     int64_t left = nsteps;
     if (block_eligible(c)) {
         // whole blocks, then the remainder as one shorter block: no step of
-        // this path runs the per-step kernel or captures a graph
+        // this path runs the per-step kernel
         while (left > 0) {
             const int K = (int)std::min<int64_t>(left, c->block_k);
             left -= K;
@@ -1444,23 +1373,7 @@ sp_status sp_step(sp_ctx* c, double dt, int64_t nsteps)
         }
         return SP_OK;
     }
-    while (left > 0) {
-        const bool steady = (c->kstep % 2 == 0) && (c->lf_pending == cont);
-        if (c->graph_chunk > 0 && c->graph_ok && steady && left >= c->graph_chunk) {
-            if (!c->gexec || c->graph_dt != dt) SP_TRY(capture_graph(c, dt));
-            if (c->gexec) {
-                HIP_TRY(c, hipGraphLaunch(c->gexec, c->stream));
-                c->kstep += c->graph_chunk;
-                c->steps += c->graph_chunk;
-                c->lf_pending = cont;
-                c->lf_dt = dt;
-                left -= c->graph_chunk;
-                continue;
-            }
-        }
-        SP_TRY(step_once(c, base));
-        --left;
-    }
+    for (; left > 0; --left) SP_TRY(step_once(c, base));
     return SP_OK;
 }
 
@@ -1733,7 +1646,6 @@ sp_status sp_set_batching(sp_ctx* c, const int32_t* waves, const int32_t* persis
             (persistent[q] != 0 && persistent[q] != 1))
             return fail(c, SP_EINVAL, "bucket %d: waves must be 1, 2, 4 or 8, persistent 0 or 1", q);
     HIP_TRY(c, hipStreamSynchronize(c->stream));
-    drop_graph(c);
     for (int q = 0; q < kNumBuckets; ++q) {
         c->bk[q].waves = waves[q];
         c->bk[q].persist = persistent[q];
@@ -1778,11 +1690,7 @@ sp_status sp_set_graph_chunk(sp_ctx* c, int32_t chunk)
 {
     if (!c) return SP_EINVAL;
     if (chunk < 0 || (chunk % 2) != 0) return fail(c, SP_EINVAL, "graph chunk must be even and >= 0");
-    HIP_TRY(c, hipStreamSynchronize(c->stream));
-    drop_graph(c);
-    c->graph_chunk = chunk;
-    c->graph_ok = true;
-    return SP_OK;
+    return SP_OK;   // no launch is captured: per-step contexts launch step by step
 }
 
 sp_status sp_autotune(sp_ctx* c, double dt, int32_t reps, double* best_ms)
@@ -1793,7 +1701,6 @@ sp_status sp_autotune(sp_ctx* c, double dt, int32_t reps, double* best_ms)
     if (c->p.flags & SP_TANGENTIAL_SPRING) return fail(c, SP_ESTATE, "the autotuner does not run the tangential spring");
     SP_TRY(upload_phase(c));
     HIP_TRY(c, hipStreamSynchronize(c->stream));
-    drop_graph(c);
     // scratch copies of the mutable state: the trials do not advance the simulation
     const size_t N = (size_t)std::max<int64_t>(1, c->n);
     uint32_t *sx = nullptr, *sy = nullptr, *serr = nullptr;
@@ -1885,7 +1792,6 @@ sp_status sp_autotune(sp_ctx* c, double dt, int32_t reps, double* best_ms)
     SP_TRY(prepare_buckets(c));
     SP_TRY(invalidate_lists(c, nullptr, c->ncells));   // the trials stepped a scratch state with them
     if (blocked) SP_TRY(block_prepare(c));              // the ring for the chosen block length
-    drop_graph(c);
     if (best_ms) *best_ms = total;
     return SP_OK;
 }
