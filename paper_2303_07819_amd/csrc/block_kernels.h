@@ -149,6 +149,13 @@ __device__ __forceinline__ double row_sum5(const double (&v)[5], int lane)
     return x + dpp_perm<0xb1>(x);
 }
 
+// Static LDS of dem_block_kernel<., W, .>: its arrays wsum, wdisp and rows.  A
+// launch's dynamic LDS has to leave room for it.
+constexpr size_t block_static_lds(int W)
+{
+    return (size_t)W * sizeof(int) + 2 * (size_t)W * sizeof(float) + 2 * (kRing + 1) * 4 * (size_t)W * sizeof(double);
+}
+
 // W: the most wavefronts of a launch (4, 8 or 16); a.work, a.cap and the
 // launch's threads belong to one run of cells.
 template <int SCHED, int W, bool TSP = false>

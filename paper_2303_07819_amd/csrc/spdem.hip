@@ -475,8 +475,12 @@ template <int SCHED, int W, bool PERSIST>
 sp_status prepare_t(sp_ctx* c, int threads, size_t lds, int cap, int* resident)
 {
     const int BT = threads;
-    const void* k = cap <= 64 * W ? (const void*)dem_step_kernel<SCHED, W, PERSIST, true>
-                                  : (const void*)dem_step_kernel<SCHED, W, PERSIST, false>;
+    const bool one = cap <= 64 * W;
+    const void* k = one ? (const void*)dem_step_kernel<SCHED, W, PERSIST, true>
+                        : (const void*)dem_step_kernel<SCHED, W, PERSIST, false>;
+    if (c->p.flags & SP_TANGENTIAL_SPRING)
+        k = one ? (const void*)dem_step_kernel<SCHED, W, false, true, true>
+                : (const void*)dem_step_kernel<SCHED, W, false, false, true>;
     if (lds > 65536) HIP_TRY(c, hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
     int per_cu = 0;
     HIP_TRY(c, hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k, BT, lds));
@@ -535,16 +539,19 @@ sp_status launch_block_t(sp_ctx* c, hipStream_t st, const BlockArgs& a, int grid
     return launch_block_tt<SCHED, W, false>(c, st, a, grid, threads, lds);
 }
 
+// Wavefronts of the kernel variant that runs cells of up to `waves`.
+int block_variant(int waves) { return waves <= 4 ? 4 : waves <= 8 ? 8 : 16; }
+
 sp_status launch_block_sel(sp_ctx* c, hipStream_t st, int sched, int waves, const BlockArgs& a, int grid,
                            int threads, size_t lds)
 {
     const bool binned = sched == SP_SCHED_BINNED;
     if (waves < 1 || waves > 16) return fail(c, SP_EINVAL, "no blocked kernel for waves=%d", waves);
-    if (waves <= 4)
-        return binned ? launch_block_t<2, 4>(c, st, a, grid, threads, lds) : launch_block_t<1, 4>(c, st, a, grid, threads, lds);
-    if (waves <= 8)
-        return binned ? launch_block_t<2, 8>(c, st, a, grid, threads, lds) : launch_block_t<1, 8>(c, st, a, grid, threads, lds);
-    return binned ? launch_block_t<2, 16>(c, st, a, grid, threads, lds) : launch_block_t<1, 16>(c, st, a, grid, threads, lds);
+    switch (block_variant(waves)) {
+    case 4: return binned ? launch_block_t<2, 4>(c, st, a, grid, threads, lds) : launch_block_t<1, 4>(c, st, a, grid, threads, lds);
+    case 8: return binned ? launch_block_t<2, 8>(c, st, a, grid, threads, lds) : launch_block_t<1, 8>(c, st, a, grid, threads, lds);
+    default: return binned ? launch_block_t<2, 16>(c, st, a, grid, threads, lds) : launch_block_t<1, 16>(c, st, a, grid, threads, lds);
+    }
 }
 
 size_t bucket_group_bytes(const sp_ctx* c, const Bucket& b)
@@ -627,6 +634,14 @@ size_t block_cell_bytes(const sp_ctx* c, int cap)
     return b;
 }
 
+// Whether cells of up to cap floes fit a blocked launch's LDS, its static part
+// included (with the spring 164 B per floe beside 6.3 KB: up to 960 floes, a few
+// less with the sub-bins of a binned search).
+bool block_fits(const sp_ctx* c, int cap)
+{
+    return block_cell_bytes(c, cap) + block_static_lds(block_variant((cap + 63) / 64)) <= kBlockLdsMax;
+}
+
 // The arguments of a blocked launch that do not depend on the bucket, from the
 // step arguments.
 BlockArgs block_args_of(const StepArgs& a, double* ring, int K, const BlockNudge& nd)
@@ -702,7 +717,7 @@ sp_status launch_blocks(sp_ctx* c, const StepArgs& base, double* ring, int K, co
     for (int q = 0; q < kNumBuckets; ++q) {   // every bucket checked before any launch
         const Bucket& b = bk[q];
         if (b.cells_h.empty()) continue;
-        if (block_cell_bytes(c, b.cap) > kBlockLdsMax)
+        if (!block_fits(c, b.cap))
             return fail(c, SP_ECAPACITY, "%d floes per cell exceed the LDS of a blocked launch", b.cap);
         const size_t runs = K >= kRunSteps ? b.segs.size() : 1;
         for (size_t g = 0; g < runs; ++g) {
@@ -779,7 +794,7 @@ bool block_eligible(const sp_ctx* c)
     // with the tangential spring, while every bucket's cells fit a blocked launch's LDS
     if (c->p.flags & SP_TANGENTIAL_SPRING)
         for (const auto& b : c->bk)
-            if (!b.cells_h.empty() && block_cell_bytes(c, b.cap) > kBlockLdsMax) return false;
+            if (!b.cells_h.empty() && !block_fits(c, b.cap)) return false;
     return true;
 }
 
