@@ -68,6 +68,7 @@ struct sp_gdem {
     unsigned long long* contacts_d = nullptr;   // [kContactSlots x kContactStride], their sum counts
     int64_t steps = 0;
     Staging staging;                   // read-outs
+    std::mutex reads;                  // held by the read-outs that use the other buffer or the coarse arrays as scratch
 };
 
 namespace spdem {
@@ -1115,6 +1116,7 @@ sp_status sp_gdem_read_floes(sp_gdem* g, uint32_t* xi, uint32_t* yi, float* u, f
 {
     if (!g) return SP_EINVAL;
     if (!g->have_floes) return gfail(g, SP_ESTATE, "no floes");
+    std::lock_guard<std::mutex> lock(g->reads);
     const int n = (int)g->n, c = g->cur, o = c ^ 1;
     // into the arrays of the other buffer, one after the other
     uint32_t* s0 = reinterpret_cast<uint32_t*>(g->P[o]);
@@ -1142,6 +1144,7 @@ sp_status sp_gdem_coarse_moments(sp_gdem* g, int32_t nxc, int32_t nyc, double* o
     if (!g->have_floes) return gfail(g, SP_ESTATE, "no floes");
     if (nxc < 1 || nyc < 1 || (int64_t)nxc * nyc > (1 << 26) || !out)
         return gfail(g, SP_EINVAL, "coarse grid %d x %d out of range or null output", nxc, nyc);
+    std::lock_guard<std::mutex> lock(g->reads);
     SP_TRY(gupload_phase(g));
     const int n = (int)g->n, c = g->cur;
     const int ncoarse = nxc * nyc;
@@ -1188,6 +1191,7 @@ sp_status sp_gdem_read_order(sp_gdem* g, int32_t* ids, int32_t* starts, int64_t*
 {
     if (!g) return SP_EINVAL;
     if (!g->have_floes) return gfail(g, SP_ESTATE, "no floes");
+    std::lock_guard<std::mutex> lock(g->reads);
     const size_t N = (size_t)g->n, nb = (size_t)g->nbx * g->nby;
     if (ids) {
         int32_t* s = reinterpret_cast<int32_t*>(g->P[g->cur ^ 1]);

@@ -46,8 +46,11 @@ __global__ __launch_bounds__(256) void readout_kernel(ReadParts a, unsigned char
 
 namespace {
 
-// The pinned buffer of one object (a simulation, a network, a global DEM).
+// The pinned buffer of one object (a simulation, a network, a global DEM).  A
+// read-out holds `mu` from reserving the buffer to its last copy out of it:
+// threads that read the same object out take turns.
 struct Staging {
+    std::mutex mu;
     unsigned char* host = nullptr;
     size_t cap = 0;
 
@@ -96,6 +99,7 @@ public:
     bool run(Staging& s, hipStream_t stream, hipError_t& err)
     {
         err = hipSuccess;
+        std::lock_guard<std::mutex> lock(s.mu);
         const bool staged = parts_ > 0 && s.reserve(bytes_);
         if (staged) {
             const unsigned blocks = (unsigned)std::min<size_t>((most_ + 1023) / 1024, 256);

@@ -1469,6 +1469,7 @@ sp_status sp_read_moments(sp_ctx* c, int32_t which, double* out)
     if (which == SP_MOMENTS_DEM) {
         StepArgs a = make_args(c, 0.0);
         const size_t bytes = (size_t)nc * SP_NMOM * sizeof(double);
+        std::lock_guard<std::mutex> lock(c->staging.mu);
         if (nc > 0 && c->staging.reserve(bytes + sizeof(uint32_t))) {
             uint32_t* const e = reinterpret_cast<uint32_t*>(c->staging.host + bytes);
             hipLaunchKernelGGL(stats_read_kernel, dim3(nc), dim3(256), 0, c->stream, a,
