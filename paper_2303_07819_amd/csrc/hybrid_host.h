@@ -733,12 +733,16 @@ sp_status sp_step_hybrid(sp_ctx* c, double dt, int64_t nsteps)
             if (!ring)
                 for (auto& b : h->bk) SP_TRY(launch_bucket(c, b, base, k, false));
             double* const Qn = c->Q[(k + 1) & 1];
-            const ClosureArgs ca = closure_args(c, c->t_now);
-            hipLaunchKernelGGL(hybrid_cells_kernel, dim3((c->ncells + 63) / 64), dim3(64), 0, c->stream, st,
-                               const_cast<double*>(st.ub), const_cast<double*>(st.vb), c->Q[k & 1], Qn, h->Qf, h->tail,
-                               h->row_d, ca, c->desc, h->net_window, dt, inv_area, c->cfl_bits_d, c->err_d);
-            HIP_TRY(c, hipGetLastError());
-            if (nclos > 0) {
+            if (nclos == 0) {   // every cell in DEM mode: the plain update
+                hipLaunchKernelGGL(lf_kernel, dim3((c->ncells + 63) / 64), dim3(64), 0, c->stream, st, c->Q[k & 1], Qn,
+                                   c->p.nx, c->p.ny, dt, c->p.cell_lx, c->p.cell_ly, inv_area, c->cfl_bits_d, c->err_d, 0);
+                HIP_TRY(c, hipGetLastError());
+            } else {
+                const ClosureArgs ca = closure_args(c, c->t_now);
+                hipLaunchKernelGGL(hybrid_cells_kernel, dim3((c->ncells + 63) / 64), dim3(64), 0, c->stream, st,
+                                   const_cast<double*>(st.ub), const_cast<double*>(st.vb), c->Q[k & 1], Qn, h->Qf,
+                                   h->tail, h->row_d, ca, c->desc, h->net_window, dt, inv_area, c->cfl_bits_d, c->err_d);
+                HIP_TRY(c, hipGetLastError());
                 const sp_status ns = mlp_stage(h->net, c->stream);
                 if (ns) return fail(c, ns, "closure network: %s", h->net->err.c_str());
                 hipLaunchKernelGGL(hybrid_forward_kernel, dim3((unsigned)mlp_blocks(h->net, nclos)),
