@@ -321,9 +321,12 @@ sp_status sp_set_batching(sp_ctx* ctx, const int32_t* waves, const int32_t* pers
  * buckets.  *best_ms may be NULL.  Synchronises.
  * Errors: SP_EINVAL, SP_ESTATE, SP_ENOMEM, SP_EDEVICE. */
 sp_status sp_autotune(sp_ctx* ctx, double dt, int32_t reps, double* best_ms);
-/* Nominal wavefronts per cell of each bucket's blocked launches (0 for an empty
- * bucket): what its largest cell count can need, rounded to the next of 1, 2,
- * 4, 8, 16.  A launch takes ceil(n / 64) for its own cells (<= this). */
+/* Wavefronts per cell of each bucket's blocked launches (0 for an empty bucket):
+ * ceil(n / 64) of its largest cell, rounded up to 1, 2, 4, 8 or 16; sp_set_batching
+ * does not change it.  Cells launched together take ceil(n / 64) wavefronts of the
+ * largest of them (<= this): a launch of fewer than 4 steps takes a bucket's cells
+ * together, longer ones take runs of cells of one number, a run of fewer than 256
+ * cells with the cells after it. */
 sp_status sp_get_block_waves(sp_ctx* ctx, int32_t* waves);
 
 /* Temporal blocking of the plain step (coarse step = fine step): with k > 1,

@@ -318,7 +318,7 @@ class Sim:
         return float(best.value)
 
     def block_waves(self):
-        """Wavefronts per cell of each bucket's blocked launches (0: empty bucket)."""
+        """Wavefronts per cell of each bucket's blocked launches, rounded up to a power of two (0: empty bucket)."""
         w = np.zeros(NUM_BUCKETS, np.int32)
         self._check(self._lib.sp_get_block_waves(self._h, _p(w)))
         return w

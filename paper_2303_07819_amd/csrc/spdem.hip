@@ -602,16 +602,6 @@ sp_status launch_bucket(sp_ctx* c, const Bucket& b, const StepArgs& base, int64_
     return launch_sel(c, c->sched, b.waves, persist, a, grid, bucket_threads(c, b), bucket_lds(c, b));
 }
 
-// Upper limit of the wavefronts per cell of a bucket's blocked launches, which
-// take one per 64 floes: the bucket's own W when its cells have at most 64 W
-// floes, else the smaller of 8 and 16 that holds one floe per lane (up to the
-// 1024-floe cell limit).
-int block_waves(const Bucket& b)
-{
-    if (b.cap <= 64 * b.waves) return b.waves;
-    return b.cap <= 512 ? 8 : 16;
-}
-
 // LDS of one cell of a blocked launch: per floe its position and radius, its
 // velocity (16 B each; the sorted copy of a binned search lies over the
 // velocities), its candidates and their count; the sub-bins of a binned search;
@@ -1815,7 +1805,11 @@ sp_status sp_autotune(sp_ctx* c, double dt, int32_t reps, double* best_ms)
 sp_status sp_get_block_waves(sp_ctx* c, int32_t* waves)
 {
     if (!c || !waves) return c ? fail(c, SP_EINVAL, "null waves") : SP_EINVAL;
-    for (int q = 0; q < kNumBuckets; ++q) waves[q] = c->bk[q].cells_h.empty() ? 0 : block_waves(c->bk[q]);
+    for (int q = 0; q < kNumBuckets; ++q) {
+        int w = 1;
+        while (64 * w < c->bk[q].cap) w *= 2;
+        waves[q] = c->bk[q].cells_h.empty() ? 0 : w;
+    }
     return SP_OK;
 }
 
