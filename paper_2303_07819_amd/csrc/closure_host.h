@@ -129,14 +129,15 @@ __device__ __forceinline__ void reduced_rel(int C, const double* red, const doub
     dw = q[2] / (1.0 + kw * fabs(q[2]) * tr);
 }
 
-// Statistics of cell C's reduced DEM at time t: coefficient (u, v), sources
-// per unit area (s_x, s_y, s_w).
+// Ocean current and curl at the centre of cell C (ocean_centre_kernel's table).
 __device__ __forceinline__ CellOcean centre_of(int C, const double* oc)
 {
     const double4 q = reinterpret_cast<const double4*>(oc)[C];
     return CellOcean{q.x, q.y, q.z};
 }
 
+// Statistics of cell C's reduced DEM at time t: coefficient (u, v), sources
+// per unit area (s_x, s_y, s_w).
 __device__ __forceinline__ void reduced_stats(int C, const double* red, const double* mf, const double* oc, double t,
                                               double out[5])
 {
@@ -447,8 +448,6 @@ sp_status malloc_m(sp_mlp* mm, T** p, size_t count)
     return SP_OK;
 }
 
-// Inference forward pass of M rows in one fused launch (no scratch, nothing
-// kept), on `stream`.
 // The fused forward's LDS image of the current parameters and normalisation.
 sp_status mlp_stage(sp_mlp* mm, hipStream_t stream)
 {
@@ -467,6 +466,8 @@ int64_t mlp_blocks(const sp_mlp* mm, int64_t M)
     return std::min<int64_t>((M + per_block - 1) / per_block, 2 * (int64_t)mm->num_cus);
 }
 
+// Inference forward pass of M rows in one fused launch (no scratch, nothing
+// kept), on `stream`.
 sp_status mlp_infer(sp_mlp* mm, const float* x, int64_t M, float* y, hipStream_t stream)
 {
     if (M <= 0) return SP_OK;

@@ -628,7 +628,9 @@ __global__ __launch_bounds__(256) void ckey_kernel(const uint4* P, int n, int nx
 // cell that finds fewer floes than its count scans all floes instead.  Runs of
 // 4, a cell per wavefront, while the grid is small enough for the sums before a
 // run to cost nothing (48 x 24 cells: 15.5 us, a workgroup per row 89), of 64
-// above.
+// above.  A whole read-out of 100,000 floes with runs of 4 and of 64: 128 x 128
+// cells 197 and 223 us, 256 x 128 326 and 346, 256 x 256 631 and 624, 512 x 256
+// 1153 and 1133.
 constexpr int kCoarseRun = 4, kCoarseRunLarge = 64, kCoarseSmall = 1 << 16;
 
 __global__ __launch_bounds__(256) void cpull_kernel(const int32_t* ckey, const int32_t* ccount, const int32_t* crow,

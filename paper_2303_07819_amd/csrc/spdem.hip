@@ -608,11 +608,15 @@ sp_status launch_bucket(sp_ctx* c, const Bucket& b, const StepArgs& base, int64_
 // with the tangential spring the floes' contact history.
 constexpr size_t kBlockLdsMax = 160 * 1024;
 constexpr int kMaxBlockWaves = SP_MAX_CELL_FLOES / 64;
-// A launch of fewer steps than this takes a bucket's runs together: its time is
-// its launches and reads, not the wavefronts that a cell has too many (a
-// sampling step of 64 x 64 cells of 0 to 700 floes takes 95 us with the runs
-// together, 105 apart; 32 steps of 128 x 128 such cells 2670 us apart, 2750
-// together).
+// A launch of fewer steps than this takes a bucket's runs together.  One step is
+// its launches and reads, not the wavefronts that a cell has too many: cells of 0
+// to 700 floes, a call of one step and its wait, 64 x 64 cells 137 us with the
+// runs together and 198 apart, 128 x 128 cells 357 and 424.  With two steps the
+// two are level (185 and 183; 466 and 458), with 4 apart gains 1 to 4 % (278 and
+// 268; 623 and 615) and with 32 3 % (3333 and 3250).  With cells of up to 255
+// floes apart is the faster one by 8 to 12 % throughout (one step 150 and 138, 32
+// steps 1088 and 1030), so calls of one to three steps on such grids pay for the
+// line.
 constexpr int kRunSteps = 4;
 
 size_t block_cell_bytes(const sp_ctx* c, int cap)
@@ -791,7 +795,11 @@ bool block_eligible(const sp_ctx* c)
 // Continuum steps of the next launch of a block's `left`: all of them where one
 // workgroup holds the grid; up to kLfTilesMax cells an odd number within the
 // halo (the launch writes the other buffer, which an odd number of steps ends
-// in); one where the tiles' repeated work is no longer free.
+// in); one above.  A call of 32 steps with one floe per cell, us by single launches
+// and by tiles: 64 x 64 cells 218 and 168, 128 x 128 381 and 336, 192 x 192 760 and
+// 716, 256 x 256 1226 and 1228, 384 x 384 2585 and 2621: the tiles' repeated work
+// costs what the launches saved give at 256 x 256.  The line lies on the safe side
+// of that: grids between the two give up 5 to 6 % of such a call.
 constexpr int kLfTilesMax = 128 * 128;
 
 int lf_launch_steps(const sp_ctx* c, int left)
