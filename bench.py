@@ -393,8 +393,10 @@ def dem_roofline(sim, w, profile_steps):
         1, w.nfloes * (wk1["blocked_steps"] - wk0["blocked_steps"]))
     if blocked:
         # floes resident in LDS for k_block steps: VALU binds (state read and
-        # written once per launch, statistics every step)
-        ops = valu_ops_per_floe_step(candidates_per_floe_step, contacts_per_floe_step)
+        # written once per launch, statistics every step).  The listed candidates
+        # are left out: most are decided by the displacement bound, and the kernel
+        # does not count the ones it tests
+        ops = valu_ops_per_floe_step(0.0, contacts_per_floe_step)
         tops = ops * w.nfloes / (dem_ms * 1e-3) / 1e12
         bytes_step = BYTES_PER_FLOE_STEP * w.nfloes / k_block + BYTES_PER_CELL_STEP * w.ncells
         roofline = {"bound": "alu", "kernel": "dem_block_kernel", "achieved": tops, "peak": VALU_PEAK_TOPS,
