@@ -324,6 +324,7 @@ class Sim:
         return w
 
     def set_graph_chunk(self, chunk: int):
+        """Accepted without effect (no launch is captured as a graph)."""
         self._check(self._lib.sp_set_graph_chunk(self._h, int(chunk)))
 
     def set_step_block(self, k: int):
